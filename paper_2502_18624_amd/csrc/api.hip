@@ -980,8 +980,7 @@ int lattice_init(mcl_lattice** out, int model, int64_t L, uint64_t seed, int ini
         int devid = 0;
         if (hipGetDevice(&devid) == hipSuccess) (void)noalloc_setup(devid);
     }
-    const hipError_t e = model == MCL_ISING_LUT ? mcl::launch_init1(h->g, init_state, seed, h->stream)
-                                                : mcl::launch_init(h->g, model, init_state, seed, h->stream);
+    const hipError_t e = mcl::launch_init(h->g, model, init_state, seed, h->stream);
     if (e != hipSuccess) {
         delete h;
         return hip_fail(e);

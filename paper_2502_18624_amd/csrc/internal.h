@@ -33,7 +33,6 @@ struct HalfSweepArgs {
 };
 hipError_t launch_ising_half(const Geom& g, const HalfSweepArgs& a, hipStream_t s);
 // 1-bit Ising with table-driven random bits (W = L/64, Q = L/256 in Geom).
-hipError_t launch_init1(const Geom& g, int init_state, uint64_t seed, hipStream_t s);
 // Bucket table of the 1-bit mode: kLutBucketBytes of device memory, built
 // once per beta, read by every half-sweep at that beta.
 constexpr int64_t kLutBucketBytes = 4096 * 8;

@@ -10,51 +10,51 @@ namespace {
 
 
 // ---------------------------------------------------------------------------
-// Initial state.  One thread per 32-bit word (8 cells) of one plane.
+// Initial state.  One thread per word index (row y, word wd) of both planes
+// (8 four-bit or 32 one-bit cells each): they hold the 16 (64) consecutive
+// sites from x = 16 wd (64 wd) on, so each generator block of 4 sites is
+// computed once and gives two cells of each plane -- even x those of plane
+// y & 1, odd x those of the other.  Bound by the generator's VALU work,
+// L^2 / 4 blocks.  With a block per cell it took 5.44 ms of a 1-bit quench at
+// L = 2^16 (4 sweeps, 3 measurements: 11.9 ms in all, 8.2 with this one).
 // ---------------------------------------------------------------------------
-// Word g of the two planes (plane-major, then row, then word).
-__device__ __forceinline__ uint32_t init_word(int64_t g, int64_t L, int64_t W, int model, int init_state,
-                                              uint32_t k0, uint32_t k1)
+// The cell of initial draw w: n = s + 1 (4-bit cells) or the bit [s > 0].
+template <int MODEL>
+__device__ __forceinline__ uint32_t init_cell(uint32_t w)
 {
-    const int color = (int)(g / (L * W));
-    const int64_t rem = g - (int64_t)color * L * W;
-    const int64_t y = rem / W;
-    const int64_t wd = rem - y * W;
-    uint32_t word = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int s;
-        if (init_state == 1) {
-            s = 1;
-        } else if (init_state == 2) {
-            s = -1;
-        } else if (init_state == 3) {
-            s = 0;
-        } else {
-            const int64_t i = wd * 8 + j;
-            const int64_t x = 2 * i + ((y + color) & 1);
-            const uint64_t n = (uint64_t)(y * L + x);
-            const uint64_t blk = n >> 2;
-            const Philox4 o = philox4x32_10(dev::lo32(blk), dev::hi32(blk), 0u, 4u, k0, k1);
-            const uint32_t sel = (uint32_t)(n & 3);
-            const uint32_t w = sel == 0 ? o.v0 : sel == 1 ? o.v1 : sel == 2 ? o.v2 : o.v3;
-            if (model == 0)
-                s = (w < 0x80000000u) ? 1 : -1;
-            else
-                s = (int)(((uint64_t)w * 3u) >> 32) - 1;
-        }
-        word |= (uint32_t)(s + 1) << (4 * j);
-    }
-    return word;
+    if (MODEL == 1) return (w >= 0x55555556u ? 1u : 0u) + (w >= 0xAAAAAAABu ? 1u : 0u);   // floor(3 w / 2^32)
+    return MODEL == 0 ? (~w >> 31) << 1 : ~w >> 31;                                       // +1 iff w < 2^31
 }
 
-__global__ __launch_bounds__(256) void init_kernel(uint32_t* __restrict__ planes, int64_t L, int64_t W,
-                                                   int model, int init_state, uint32_t k0, uint32_t k1)
+template <int MODEL>
+__global__ __launch_bounds__(256) void init_kernel(uint32_t* __restrict__ planes, uint64_t L, uint32_t W,
+                                                   uint32_t k0, uint32_t k1)
 {
-    const int64_t total = 2 * L * W;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total;
-         g += (int64_t)gridDim.x * blockDim.x)
-        planes[g] = init_word(g, L, W, model, init_state, k0, k1);
+    constexpr int CB = MODEL == 2 ? 1 : 4, CELLS = 32 / CB, BLOCKS = CELLS / 2;
+    const uint64_t total = L * W;
+    for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total;
+         g += (uint64_t)gridDim.x * blockDim.x) {
+        // (a 32-bit division where the indices allow it)
+        const uint64_t y = total >> 32 ? g / W : (uint32_t)g / W;
+        const uint64_t blk = g * BLOCKS;        // (y L + x) / 4, x = 2 CELLS wd and L = 2 CELLS W
+        uint32_t even = 0, odd = 0;
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b) {
+            const uint64_t n = blk + b;
+            const Philox4 o = philox4x32_10(dev::lo32(n), dev::hi32(n), 0u, 4u, k0, k1);
+            even |= init_cell<MODEL>(o.v0) << (2 * CB * b) | init_cell<MODEL>(o.v2) << (2 * CB * b + CB);
+            odd |= init_cell<MODEL>(o.v1) << (2 * CB * b) | init_cell<MODEL>(o.v3) << (2 * CB * b + CB);
+        }
+        planes[g] = (y & 1) ? odd : even;
+        planes[total + g] = (y & 1) ? even : odd;
+    }
+}
+
+// An ordered start: every word of both planes.
+__global__ __launch_bounds__(256) void fill_kernel(uint4* __restrict__ p, uint64_t n, uint32_t word)
+{
+    for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n; g += (uint64_t)gridDim.x * blockDim.x)
+        p[g] = make_uint4(word, word, word, word);
 }
 
 // The sweep index of a launch is t, plus the device word *tbase when tbase
@@ -89,34 +89,6 @@ __global__ __launch_bounds__(256) void half_sweep_kernel(uint32_t* __restrict__ 
         dev::band_update<MODEL, 1, COLOR>(own, oth, L, rows, q, y0, t, k0, k1, hu, T4, T8, s_tab.e);
     else
         dev::band_update<MODEL, 2, COLOR>(own, oth, L, rows, q, y0, t, k0, k1, 0u, T4, T8, s_tab.e);
-}
-
-// Initial state of the 1-bit layout: one thread per word (32 cells) of one plane.
-__device__ __forceinline__ uint32_t init1_word(int64_t g, int64_t L, int64_t W, int init_state, uint32_t k0,
-                                               uint32_t k1)
-{
-    const int color = (int)(g / (L * W));
-    const int64_t rem = g - (int64_t)color * L * W;
-    const int64_t y = rem / W;
-    const int64_t wd = rem - y * W;
-    if (init_state == 1) return 0xFFFFFFFFu;
-    if (init_state == 2) return 0u;
-    uint32_t word = 0;
-    for (int j = 0; j < 32; ++j) {
-        const int64_t x = 2 * (wd * 32 + j) + ((y + color) & 1);
-        const uint64_t n = (uint64_t)(y * L + x);
-        const Philox4 o = philox4x32_10(dev::lo32(n >> 2), dev::hi32(n >> 2), 0u, 4u, k0, k1);
-        word |= (philox_word(o, (int)(n & 3)) < 0x80000000u ? 1u : 0u) << j;
-    }
-    return word;
-}
-
-__global__ __launch_bounds__(256) void init1_kernel(uint32_t* __restrict__ planes, int64_t L, int64_t W,
-                                                    int init_state, uint32_t k0, uint32_t k1)
-{
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < 2 * L * W;
-         g += (int64_t)gridDim.x * blockDim.x)
-        planes[g] = init1_word(g, L, W, init_state, k0, k1);
 }
 
 // Bucket table of the 1-bit mode, one thread per bucket (the entry is
@@ -184,10 +156,24 @@ constexpr int64_t kMaxInitBlocks = int64_t(1) << 20;
 
 hipError_t launch_init(const Geom& g, int model, int init_state, uint64_t seed, hipStream_t s)
 {
-    const int64_t total = 2 * g.L * g.W;
-    const int64_t blocks = std::min<int64_t>((total + 255) / 256, kMaxInitBlocks);
-    hipLaunchKernelGGL(init_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, g.plane0, g.L, g.W, model,
-                       init_state, (uint32_t)seed, (uint32_t)(seed >> 32));
+    const int64_t words = g.plane_words();
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    if (init_state != 0) {
+        // n = 2, 0, 1 in every 4-bit cell; every bit set or clear
+        const uint32_t word = init_state == 1 ? (g.cb == 4 ? 0x22222222u : 0xFFFFFFFFu)
+                                              : init_state == 2 ? 0u : 0x11111111u;
+        const int64_t vecs = words / 2;             // of both planes
+        const dim3 grid((uint32_t)std::min<int64_t>((vecs + 255) / 256, kMaxInitBlocks));
+        hipLaunchKernelGGL(fill_kernel, grid, dim3(256), 0, s, reinterpret_cast<uint4*>(g.plane0), (uint64_t)vecs,
+                           word);
+        return hipGetLastError();
+    }
+    const dim3 grid((uint32_t)std::min<int64_t>((words + 255) / 256, kMaxInitBlocks));
+    const uint64_t L = (uint64_t)g.L;
+    const uint32_t W = (uint32_t)g.W;
+    if (model == 0) hipLaunchKernelGGL(init_kernel<0>, grid, dim3(256), 0, s, g.plane0, L, W, k0, k1);
+    else if (model == 1) hipLaunchKernelGGL(init_kernel<1>, grid, dim3(256), 0, s, g.plane0, L, W, k0, k1);
+    else hipLaunchKernelGGL(init_kernel<2>, grid, dim3(256), 0, s, g.plane0, L, W, k0, k1);
     return hipGetLastError();
 }
 
@@ -225,15 +211,6 @@ static hipError_t launch_half(const Geom& g, const HalfSweepArgs& a, hipStream_t
         if (hi0) launch_model<1, true>(grid, s, own, oth, L, R, a.color, a.t, a.tbase, k0, k1, a.T4, a.T8, tbl);
         else launch_model<1, false>(grid, s, own, oth, L, R, a.color, a.t, a.tbase, k0, k1, a.T4, a.T8, tbl);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_init1(const Geom& g, int init_state, uint64_t seed, hipStream_t s)
-{
-    const int64_t total = 2 * g.L * g.W;
-    const int64_t blocks = std::min<int64_t>((total + 255) / 256, kMaxInitBlocks);
-    hipLaunchKernelGGL(init1_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, g.plane0, g.L, g.W,
-                       init_state, (uint32_t)seed, (uint32_t)(seed >> 32));
     return hipGetLastError();
 }
 
