@@ -50,51 +50,48 @@ hipError_t launch_set_word(uint32_t* p, uint32_t v, bool add, hipStream_t s);
 // (corrupted) are L^2 minus the three counts.
 constexpr int kAccSlots = 16;
 hipError_t launch_zero(int64_t* p, int64_t n, hipStream_t s);
-// T bits of the sampled columns x = 0 mod 16: for every row y, bit j of
+// T bits of the sampled columns x = 0 mod 16: for every row y, bit j of its
 // word k is [s(16 (32 k + j), y) = +1] (and, Blume-Capel only, a second
-// plane of [s != 0] after L rows); tbits_words(L) words per row, the L / 16
+// plane of [s != 0] after the first); tbits_words(L) words per row, the L / 16
 // bits of a row repeated to fill one word below L = 512 (L is a power of
 // two wherever they are used; other L get room for ceil(L / 512) words).
-// 4-bit Ising lattices have room after the L rows for the residue rows of
-// the sampled rows: row 16 b + rho holds, for y = 16 b, bit j of word k =
-// [s(16 (32 k + j) + rho, y) = +1] (written by the fused short-distance
-// tiles, read by the sampled x pass).
+// Word k of row y = 16 b + rho is at k L + rho (L / 16) + b: the rows of one
+// residue class follow each other, as the sampled y pass reads them.
+// 4-bit Ising lattices from L = 512 on have room after that plane for the
+// residue rows of the sampled rows y = 16 b: bit j of word (b tbits_words(L)
+// + k) 16 + rho is [s(16 (32 k + j) + rho, y) = +1], read by the sampled x pass.
 inline int64_t tbits_words(int64_t L) { return L >= 512 ? (L + 511) / 512 : 1; }
 inline int64_t tbits_bytes(int model, int64_t L) { return (model == 2 ? 1 : 2) * L * tbits_words(L) * 4; }
-// B, M, Q, counts and the sigma-h histogram into acc; with tbits set, also
-// the T bits of every row (written by the same pass from L = 512 on).
-hipError_t launch_bmq(const Geom& g, int model, int64_t* acc, uint32_t* tbits, hipStream_t s);
-// Correlations from every source at r = 0..R (R <= 32), LDS-tiled.  With acc
-// set (4-bit Ising cells, L >= 4096, see bmq_fused) the same tiles give what
-// launch_bmq adds to acc, and with tbits set (L a power of two) the T bits
-// and the residue rows of the sampled rows after them;
-// acc[14] then counts the workgroups that met a cell holding no spin, for
-// which the caller must run launch_bmq instead (acc zeroed, tbits null).
-hipError_t launch_corr_short(const Geom& g, int model, int R, int64_t* Cx, int64_t* Cy, int64_t* acc,
-                             uint32_t* tbits, hipStream_t s);
-// Whether measure() takes B/M/Q from the short-distance tiles when it runs
-// them: 4-bit Ising cells at L >= 4096, unless the environment variable
-// MCL_MEASURE_FUSED is 0 (read at every call).  For 1-bit cells the B/M/Q
-// pass reads a quarter of the bytes and stays the cheaper way.
-bool bmq_fused(const Geom& g, int model);
+// B, M, Q, counts and the sigma-h histogram into acc, from the cells alone.
+hipError_t launch_bmq(const Geom& g, int model, int64_t* acc, hipStream_t s);
+// The measurement pass: correlations from every source at r = 0 .. 32 into
+// Cx and Cy (33 sums each); with acc set the counts #(+1) [2] and #(0) [4],
+// the sigma-h histogram [5 .. 13], and in [14] the number of waves that met a
+// cell holding no spin, for which the caller must run launch_bmq instead (acc
+// zeroed); with tbits set (L >= 512, a power of two) the T bits and with
+// rbits set (4-bit Ising) the residue rows.
+hipError_t launch_pass(const Geom& g, int model, int64_t* Cx, int64_t* Cy, int64_t* acc, uint32_t* tbits,
+                       uint32_t* rbits, hipStream_t s);
+// The T bits of a lattice below L = 512.
+hipError_t launch_tbits(const Geom& g, int model, uint32_t* tbits, hipStream_t s);
+// Whether measure() takes B/M/Q from the measurement pass when it runs it:
+// yes, unless the environment variable MCL_MEASURE_FUSED is 0 (read at every
+// call; a test compares the two).
+bool bmq_fused();
 // Correlations from every source at distances r[0..nr) (any r <= L/2).
 hipError_t launch_corr_all(const Geom& g, const int32_t* r_dev, int nr, int64_t* Cx, int64_t* Cy,
                            hipStream_t s);
-// Correlations from the sampled sources x = y = 0 (mod 16) at r[0..nr), from
-// the lattice (x) and the T bits of the B/M/Q pass (y).
+// Correlations from the sampled sources x = y = 0 (mod 16) at r[0..nr).
 struct SampledArgs {
     const int32_t* r;
     int nr;
     int64_t* Cx;
     int64_t* Cy;
     const uint32_t* tbits;
-    const uint32_t* rbits = nullptr;    // residue rows (4-bit Ising, written by the fused tiles), or null
-    int nlin = 0;                       // r[0 .. nlin) = rlin0, rlin0 + 1, ... (consecutive distances)
-    uint32_t rlin0 = 0;
+    const uint32_t* rbits = nullptr;    // residue rows (4-bit Ising from L = 512 on), or null
 };
 // The sampled sources' two passes: x (the lattice's sampled rows, or the
-// residue rows when rbits is set) and y (the T bits only).  They are
-// independent, so the caller may run them on two streams.
+// residue rows when rbits is set) and y (the T bits only).
 hipError_t launch_corr_sampled_x(const Geom& g, int model, const SampledArgs& a, hipStream_t s);
 hipError_t launch_corr_sampled_y(const Geom& g, int model, const SampledArgs& a, hipStream_t s);
 

@@ -1,5 +1,6 @@
-// Measurement kernels for gfx950: B, M, Q, counts and the Schwinger-Dyson
-// histogram; the correlation sums of section 3.3.
+// Measurement kernels for gfx950 beside the measurement pass (pass.hip): B,
+// M, Q, counts and the Schwinger-Dyson histogram alone; the correlation sums
+// of section 3.3 from every source beyond r = 32 and from the sampled ones.
 //
 // Energy-like sums.  Every bond of the periodic lattice joins a colour-0 and
 // a colour-1 site (L even), so the bond sum B is the sum over colour-0 cells
@@ -14,16 +15,13 @@
 //   along x the partner (x + r, y) is in plane c ^ (r & 1) at in-plane index
 //   i + m with m = r / 2 (r even) or (r - 1) / 2 + ((y + c) & 1) (r odd), a
 //   funnel shift of two neighbouring words.
-// Every-source distances r <= 32 run from an LDS tile of both planes with 32
-// halo rows; longer every-source distances (full mode) read partners from
-// global memory.  The sampled sources (x = y = 0 mod 16) are cell 0 of
-// every word of the rows y = 0 mod 16 of plane 0: along x each source row is
-// unpacked to one int8 per site in LDS; along y the work runs over target
-// rows against a compact int8 copy of the sources, four products per dot4.
+// The sampled sources (x = y = 0 mod 16) are taken as bits: residue rows
+// along x, the T bits along y.
 #include <algorithm>
 #include <cstdlib>
 
 #include "internal.h"
+#include "measure_device.h"
 
 namespace mcl {
 namespace {
@@ -34,22 +32,7 @@ __global__ void zero_kernel(int64_t* p, int64_t n)
     if (i < n) p[i] = 0;
 }
 
-__device__ __forceinline__ uint32_t pick(const uint4& v, int d)
-{
-    return d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
-}
-
 __device__ __forceinline__ uint32_t wrap(uint32_t v, uint32_t n) { return v >= n ? v - n : v; }
-
-// acc + (number of set bits of x) as one v_bcnt_u32_b32.  Written out, sums
-// of several bit counts are re-associated into separate counts and
-// three-input adds.
-__device__ __forceinline__ uint32_t bcnt_acc(uint32_t x, uint32_t acc)
-{
-    uint32_t r;
-    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(acc));
-    return r;
-}
 
 // Per-word cell counts: +1 (n = 2), -1 (n = 0), 0 (n = 1); anything else is
 // what they leave.  Bit 0 of each nibble carries the test; the mask of the
@@ -144,28 +127,6 @@ __device__ __forceinline__ void block_add(const int64_t (&v)[N], int64_t* __rest
     __syncthreads();
 }
 
-// As block_add for 2 N values: v[0..N) go to X, v[N..2N) to Y.
-template <int N>
-__device__ __forceinline__ void block_add_xy(const int64_t (&v)[2 * N], int64_t* __restrict__ X,
-                                             int64_t* __restrict__ Y, int64_t (*lds)[2 * N])
-{
-    const int wave = threadIdx.x >> 6;
-    const int nwaves = blockDim.x >> 6;
-#pragma unroll
-    for (int i = 0; i < 2 * N; ++i) {
-        const int64_t s = wave_sum(v[i]);
-        if ((threadIdx.x & 63) == 0) lds[wave][i] = s;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 2 * N; i += blockDim.x) {
-        int64_t tot = 0;
-        for (int w = 0; w < nwaves; ++w) tot += lds[w][i];
-        int64_t* dst = i < N ? &X[i] : &Y[i - N];
-        if (tot != 0) atomicAdd((unsigned long long*)dst, (unsigned long long)tot);
-    }
-    __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
 // B, M, Q, counts.  One thread per 16-byte column of plane 0, walking a
 // band of rows with plane 1's rows y - 1, y, y + 1 in registers.
@@ -228,51 +189,6 @@ __device__ __forceinline__ void sd_add_ising4(uint32_t o, uint32_t a, uint32_t b
     e[3] = bcnt_acc(S & 0x88888888u, e[3]);
 }
 
-// T bits (the sampled columns, see below) of row y from the thread's
-// vector v of the row's colour-(y & 1) plane: 4-bit cells, vector q holds
-// the cells 8 a for a = 4 q .. 4 q + 3 at nibble 0 of its words, and 8 lanes
-// make one word; 1-bit cells, vector q holds a = 16 q .. 16 q + 15 at bits
-// 0, 8, 16, 24 of its words, and 2 lanes make one word.  The lanes of a
-// word share the row (Q is a multiple of 8, resp. 2, from L = 512 on).
-template <int MODEL>
-__device__ __forceinline__ void emit_tbits(const uint4& v, uint32_t q, uint32_t y, uint32_t L,
-                                           uint32_t* __restrict__ tb)
-{
-    const uint32_t NSW = L >> 9;
-    if (MODEL == 2) {
-        uint32_t bits = 0;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t x = pick(v, d) & 0x01010101u;
-            bits |= ((x | (x >> 7) | (x >> 14) | (x >> 21)) & 0xFu) << (4 * d);
-        }
-        uint32_t w = bits << (16u * (q & 1u));
-        w |= __shfl_xor(w, 1);
-        if ((q & 1u) == 0) tb[(size_t)y * NSW + (q >> 1)] = w;
-        return;
-    }
-    uint32_t sb = 0, zb = 0;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        sb |= ((pick(v, d) >> 1) & 1u) << d;       // n = 2: s = +1
-        zb |= ((~pick(v, d)) & 1u) << d;           // n != 1: s != 0
-    }
-    const uint32_t sh = 4u * (q & 7u);
-    uint32_t ws = sb << sh, wz = zb << sh;
-    ws |= __shfl_xor(ws, 1);
-    ws |= __shfl_xor(ws, 2);
-    ws |= __shfl_xor(ws, 4);
-    if (MODEL == 1) {
-        wz |= __shfl_xor(wz, 1);
-        wz |= __shfl_xor(wz, 2);
-        wz |= __shfl_xor(wz, 4);
-    }
-    if ((q & 7u) == 0) {
-        tb[(size_t)y * NSW + (q >> 3)] = ws;
-        if (MODEL == 1) tb[(size_t)(L + y) * NSW + (q >> 3)] = wz;
-    }
-}
-
 // v of lane i + 1 (from_right) or lane i - 1 (from_left) of the wave, by a
 // DPP wave shift; the lane at the end without a neighbour gets an
 // unspecified value.
@@ -286,17 +202,15 @@ __device__ __forceinline__ uint32_t from_left(uint32_t v)
 }
 
 // One pass over both planes: B and M, Q and the value counts, and the
-// Schwinger-Dyson histogram (section 4) of sigma h over every site; with tb
-// set (L >= 512), also the T bits of every row.  A task is a column vector
-// q of a band of rows; the thread keeps rows y - 1, y, y + 1 of both
+// Schwinger-Dyson histogram (section 4) of sigma h over every site.  A task
+// is a column vector q of a band of rows; the thread keeps rows y - 1, y, y + 1 of both
 // planes.  Colour-0 sites carry the bonds (each bond has one colour-0
 // end); both colours add to the counts and the histogram.
 // WAVE_ROWS: L / (cells per vector) is a multiple of 64, so the 64 lanes of
 // a wave share their band and its row parity is a scalar.
 template <int MODEL, bool WAVE_ROWS>
 __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p0, const uint32_t* __restrict__ p1,
-                                                  uint32_t L, uint32_t rows, int64_t* __restrict__ acc,
-                                                  uint32_t* __restrict__ tb)
+                                                  uint32_t L, uint32_t rows, int64_t* __restrict__ acc)
 {
     constexpr int CB = MODEL == 2 ? 1 : 4;
     using C = Cell<CB>;
@@ -334,7 +248,6 @@ __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p
             const size_t yd = (y + 1 == L) ? 0 : y + 1;
             const uint4 adn = a4[yd * Q], bdn = b4[yd * Q];
             const bool odd = (y & 1u) != 0;      // colour-0 sites of row y have x = 2 i + (y & 1)
-            if (tb) emit_tbits<MODEL>(odd ? bmid : amid, q, y, L, tb);
             // colour 0 looks right (i + 1) on odd rows, colour 1 on even rows
             uint32_t bhalo = odd ? from_right(bmid.x) : from_left(bmid.w);
             uint32_t ahalo = odd ? from_left(amid.w) : from_right(amid.x);
@@ -399,376 +312,6 @@ __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p
 #pragma unroll
     for (int k = 0; k < 9; ++k) v[5 + k] = (int64_t)hist[k];
     block_add<14>(v, acc, red);
-}
-
-// ---------------------------------------------------------------------------
-// Correlations, every source, r = 0..R (R <= 32): LDS tile of SW words (+1 halo word
-// on the right for x-partners, +1 on the left for the B/M/Q work) by TH
-// source rows (+32 halo rows below for y-partners), both planes, with the
-// cells as 1-bit words of 32 cells: the sign bit for Ising, and for
-// Blume-Capel a second word of nonzero bits.  A 4-bit row vector (32 cells)
-// packs into one word, a 1-bit plane word is stored as it is, so every
-// model has L / 64 words per tile row.  Thread (j, g) handles word column j
-// and rows 16 g .. 16 g + 15 of the tile along one axis, for r in
-// [RLO, RHI]: per distance, axis and 32 pairs one funnel shift (x only),
-// an xor (and two ands for Blume-Capel) and the bit counts.  For 4-bit
-// Ising lattices the same tiles also give the B/M/Q sums (tile_bmq), which
-// would otherwise read the 4-bit lattice a second time.
-// ---------------------------------------------------------------------------
-constexpr int kSW = 32;
-constexpr int kTH = 64;
-constexpr int kHalo = 32;
-constexpr int kTileRows = kTH + kHalo;
-
-// Tile columns: the strip's words 0 .. kSW - 1 at CO .. CO + kSW - 1, the
-// word right of the strip after them, and with LEFT (CO = 1) the word left
-// of it at column 0 (of which only the last cell is loaded).
-template <int MODEL, bool LEFT>
-struct ShortTile {
-    static constexpr int NB = MODEL == 1 ? 2 : 1;   // bit planes: sign [, nonzero]
-    static constexpr int CO = LEFT ? 1 : 0;
-    static constexpr int COLS = kSW + 1 + CO;
-    uint32_t v[2][NB][kTileRows][COLS];
-};
-
-// Bit `BIT` (0 or 1) of each nibble of the 4 words (32 cells), in cell
-// order: bit 8 d + k of the result is nibble k of word d.  The words are
-// first interleaved (bit 4 k + d = nibble k of word d: one shift and one bit
-// select each), then the bit index is rotated from (k, d) to (d, k) by three
-// swaps of index bits (0 with 2, 1 with 3, 2 with 4) and a byte permutation
-// (3 with 4).
-template <int S, uint32_t M>
-__device__ __forceinline__ uint32_t delta_swap(uint32_t x)
-{
-    const uint32_t t = ((x >> S) ^ x) & M;
-    return x ^ t ^ (t << S);
-}
-
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
-
-template <int BIT>
-__device__ __forceinline__ uint32_t nibble_bits(const uint4& v, bool invert)
-{
-    const uint32_t s0 = BIT ? v.x >> 1 : v.x;
-    const uint32_t s1 = BIT ? v.y : v.y << 1;
-    const uint32_t s2 = v.z << (2 - BIT);
-    const uint32_t s3 = v.w << (3 - BIT);
-    uint32_t z = bit_select(0x11111111u, s0, bit_select(0x22222222u, s1, bit_select(0x88888888u, s3, s2)));
-    if (invert) z = ~z;
-    z = delta_swap<3, 0x0A0A0A0Au>(z);
-    z = delta_swap<6, 0x00CC00CCu>(z);
-    z = delta_swap<12, 0x0000F0F0u>(z);
-    return __builtin_amdgcn_perm(z, z, 0x03010200u);
-}
-
-// Column index q of a tile word, periodic in the row of Wp words (q < Wp + kSW + 1).
-__device__ __forceinline__ uint32_t wrap_col(uint32_t q, uint32_t Wp)
-{
-    return q < Wp ? q : (Wp > (uint32_t)kSW ? q - Wp : q % Wp);
-}
-
-// Tile rows row, row + step, ... (< kTileRows) of column col (lattice word
-// column qq) of both planes, as 1-bit words; tile row r is lattice row
-// y0 + r, periodic (y0 + r < L + kHalo <= 2 L).  `bad` collects the bits of
-// 4-bit Ising cells that hold no spin (n other than 0 and 2).
-template <int MODEL, class TT>
-__device__ __forceinline__ void tile_load(TT& T, const uint32_t* __restrict__ planes,
-                                          const uint4* __restrict__ P4, size_t plane_units, uint32_t Wp, uint32_t L,
-                                          uint32_t y0, uint32_t row, uint32_t step, uint32_t col, uint32_t qq,
-                                          uint32_t& bad)
-{
-    constexpr int NB = TT::NB;
-    uint32_t y = y0 + row;
-    if (y >= L) y -= L;
-    for (; row < (uint32_t)kTileRows; row += step) {
-#pragma unroll
-        for (uint32_t c = 0; c < 2; ++c) {
-            const size_t at = c * plane_units + (size_t)y * Wp + qq;
-            if (MODEL == 2) {
-                T.v[c][0][row][col] = planes[at];
-            } else {
-                const uint4 v = P4[at];
-                T.v[c][0][row][col] = nibble_bits<1>(v, false);                    // n = 2: s = +1
-                if (MODEL == 1) T.v[c][NB - 1][row][col] = nibble_bits<0>(v, true);   // n != 1
-                if (MODEL == 0) bad |= (v.x | v.y | v.z | v.w) & 0xDDDDDDDDu;
-            }
-        }
-        y += step;
-        if (y >= L) y -= L;
-    }
-}
-
-// Column 0 of tile row `row` (lattice word column qq) of both planes, for
-// 4-bit cells: the B/M/Q work uses only its last cell (the i - 1 neighbour
-// of the strip's cell 0), so one 4-byte load of the vector's last word gives
-// it (cell 31 is nibble 7 of that word, its sign bit bit 29).
-template <class TT>
-__device__ __forceinline__ void tile_load_left(TT& T, const uint4* __restrict__ P4, size_t plane_units, uint32_t Wp,
-                                               uint32_t L, uint32_t y0, uint32_t row, uint32_t qq)
-{
-    uint32_t y = y0 + row;
-    if (y >= L) y -= L;
-#pragma unroll
-    for (uint32_t c = 0; c < 2; ++c) {
-        const uint32_t w = reinterpret_cast<const uint32_t*>(P4 + c * plane_units + (size_t)y * Wp + qq)[3];
-        T.v[c][0][row][0] = ((w >> 29) & 1u) << 31;
-    }
-}
-
-// Distances [RLO, RHI] along one axis (AXIS 0: x, 1: y) for the cells of
-// plane C in tile row lr (PAR: parity of y + C).
-template <int MODEL, int AXIS, int RLO, int RHI, int C, int PAR, class TT>
-__device__ __forceinline__ void short_row(const TT& T, int lr, int j, int (&acc)[33])
-{
-    constexpr int Z = TT::NB - 1;                       // plane of nonzero bits (Blume-Capel)
-    const int jc = j + TT::CO;                          // the strip's word j in the tile
-    const uint32_t o = T.v[C][0][lr][jc];
-    const uint32_t oz = MODEL == 1 ? T.v[C][Z][lr][jc] : 0u;
-    uint32_t w0[2], w1[2], z0[2], z1[2];
-    if (AXIS == 0) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            w0[p] = T.v[p][0][lr][jc];
-            w1[p] = T.v[p][0][lr][jc + 1];
-            z0[p] = MODEL == 1 ? T.v[p][Z][lr][jc] : 0u;
-            z1[p] = MODEL == 1 ? T.v[p][Z][lr][jc + 1] : 0u;
-        }
-    }
-#pragma unroll
-    for (int r = RLO; r <= RHI; ++r) {
-        const int pc = C ^ (r & 1);
-        uint32_t pv, pz = 0;
-        if (AXIS == 0) {
-            const int m = (r & 1) ? ((r - 1) >> 1) + PAR : (r >> 1);     // in-plane shift, 0..16
-            pv = m ? funnel(w1[pc], w0[pc], m) : w0[pc];
-            if (MODEL == 1) pz = m ? funnel(z1[pc], z0[pc], m) : z0[pc];
-        } else {
-            pv = T.v[pc][0][lr + r][jc];
-            if (MODEL == 1) pz = T.v[pc][Z][lr + r][jc];
-        }
-        if (MODEL != 1) {
-            acc[r] += (int)popc(o ^ pv);                // pairs of opposite sign
-        } else {
-            const uint32_t nz = pz & oz;
-            acc[r] += (int)popc(nz) - 2 * (int)popc(nz & (o ^ pv));
-        }
-    }
-}
-
-// Distances [RLO, RHI] along one axis over the thread's kTH / 4 rows of the tile.
-template <int MODEL, int AXIS, int RLO, int RHI, class TT>
-__device__ __forceinline__ void short_chunk(const TT& T, int j, int g, int (&acc)[33])
-{
-    // tile rows G g .. G g + G - 1 (G = kTH / 4); the tile's first row is
-    // even, so the parity of y + c is that of the local row + c
-    constexpr int G = kTH / 4;
-    for (int k = 0; k < G; k += 2) {
-        const int lr = G * g + k;
-        short_row<MODEL, AXIS, RLO, RHI, 0, 0>(T, lr, j, acc);
-        short_row<MODEL, AXIS, RLO, RHI, 1, 1>(T, lr, j, acc);
-        short_row<MODEL, AXIS, RLO, RHI, 0, 1>(T, lr + 1, j, acc);
-        short_row<MODEL, AXIS, RLO, RHI, 1, 0>(T, lr + 1, j, acc);
-    }
-}
-
-template <int MODEL, int AXIS, class TT>
-__device__ __forceinline__ void short_tile(const TT& T, int j, int g, int R, int (&acc)[33])
-{
-    // r = 0 counts no pair of opposite sign for Ising cells (acc[0] stays 0)
-    short_chunk<MODEL, AXIS, MODEL == 1 ? 0 : 1, 10>(T, j, g, acc);
-    if (R > 10) short_chunk<MODEL, AXIS, 11, 21>(T, j, g, acc);
-    if (R > 21) short_chunk<MODEL, AXIS, 22, 32>(T, j, g, acc);
-}
-
-// The B/M/Q pass on a tile's 1-bit words (4-bit Ising cells): the sites
-// of tile rows 1 .. kTH (lattice rows y0 + 1 .. y0 + kTH, so every row once
-// over the strip's tiles), word column j, both planes; the thread takes rows
-// 1 + f, 9 + f, ... (f = tid / 32, so the two halves of a wave read
-// adjacent rows).  Per word of 32 cells the four neighbour words (other
-// plane: rows r - 1, r + 1, the same index, and index i + 1 or i - 1 by the
-// parity of y + c) give the sigma-h bins as in the B/M/Q pass; the +1 cells
-// are the set sign bits; the T bits of row y are bits 0, 8, 16, 24 of the
-// words of plane y & 1 (the sampled columns x = 0 mod 16), merged over 8
-// lanes into one word.
-template <int MODEL, class TT>
-__device__ __forceinline__ void tile_bmq(const TT& T, uint32_t y0, uint32_t q0, uint32_t L,
-                                         uint32_t Wp, int j, uint32_t* __restrict__ tb, uint32_t (&hist)[9],
-                                         uint32_t& np1, uint32_t& sites)
-{
-    static_assert(TT::CO == 1, "the B/M/Q work needs the word left of the strip");
-    const uint32_t NSW = L >> 9;
-    const int jc = j + 1;
-    const bool in_strip = q0 + (uint32_t)j < Wp;
-    for (uint32_t r = 1 + (threadIdx.x >> 5); r <= (uint32_t)kTH; r += 8) {
-        if (in_strip) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const uint32_t o = T.v[c][0][r][jc];
-                const uint32_t same = T.v[1 - c][0][r][jc];
-                const uint32_t up = T.v[1 - c][0][r - 1][jc], dn = T.v[1 - c][0][r + 1][jc];
-                // y0 is even, so y + c has the parity of r + c; colour 0
-                // looks right (i + 1) on odd rows, colour 1 on even rows
-                const uint32_t side = ((r + c) & 1u) ? funnel(T.v[1 - c][0][r][jc + 1], same, 1)
-                                                     : funnel(same, T.v[1 - c][0][r][jc - 1], 31);
-                sd_add1(o, up, dn, same, side, hist);
-                np1 = bcnt_acc(o, np1);
-            }
-            sites += 64;
-        }
-        if (tb) {
-            // protocol lattices (L a power of two >= 4096): every lane of the
-            // strip is in it.  Lane 8 m + 7 of a DPP row gathers lanes
-            // 8 m .. 8 m + 7 by three shifts within the row.
-            const uint32_t x = T.v[r & 1u][0][r][jc] & 0x01010101u;
-            uint32_t w = ((x | (x >> 7) | (x >> 14) | (x >> 21)) & 0xFu) << (4 * (j & 7));
-            w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x111, 0xF, 0xF, true);   // row_shr:1
-            w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x112, 0xF, 0xF, true);   // row_shr:2
-            w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x114, 0xF, 0xF, true);   // row_shr:4
-            uint32_t y = y0 + r;
-            if (y >= L) y -= L;
-            if ((j & 7) == 7) tb[(size_t)y * NSW + ((q0 + (uint32_t)j) >> 3)] = w;
-        }
-    }
-}
-
-// The residue rows of the tile's sampled rows (y = 16 b: tile rows 16, 32,
-// 48, 64, as y0 is a multiple of 64): thread (plane c, row 16 (s + 1), word
-// j) takes the bits t, t + 8, t + 16, t + 24 of its word for t = 0 .. 7,
-// the cells 16 a + 2 t + c of the row (x = 2 i + c on even rows, i = 8 a + t),
-// and merges them over 8 lanes into word (q0 + j) / 8 of residue row
-// 16 b + 2 t + c, as for the T bits.  Protocol lattices only (L a power of
-// two >= 4096: every lane of the strip is in it).
-template <class TT>
-__device__ __forceinline__ void tile_residues(const TT& T, uint32_t y0, uint32_t q0, uint32_t L,
-                                              uint32_t* __restrict__ rb)
-{
-    const uint32_t NSW = L >> 9;
-    const uint32_t c = threadIdx.x >> 7, r = 16 * (((threadIdx.x >> 5) & 3u) + 1);
-    const uint32_t j = threadIdx.x & 31u;
-    const uint32_t word = T.v[c][0][r][j + TT::CO];
-    uint32_t y = y0 + r;
-    if (y >= L) y -= L;
-    uint32_t* row = rb + (size_t)y * NSW + ((q0 + j) >> 3);       // y = 16 b: residue row 16 b + rho
-#pragma unroll 1
-    for (uint32_t t = 0; t < 8; ++t) {
-        const uint32_t x = (word >> t) & 0x01010101u;
-        uint32_t w = ((x | (x >> 7) | (x >> 14) | (x >> 21)) & 0xFu) << (4 * (j & 7));
-        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x111, 0xF, 0xF, true);   // row_shr:1
-        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x112, 0xF, 0xF, true);   // row_shr:2
-        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x114, 0xF, 0xF, true);   // row_shr:4
-        if ((j & 7) == 7) row[(size_t)(2 * t + c) * NSW] = w;
-    }
-}
-
-// Persistent over tiles: each workgroup loads tiles (strip of kSW words by
-// kTH rows, both planes, with halos) in turn and keeps its per-distance sums
-// in registers; one atomic per value per workgroup at the end.  FUSED (4-bit
-// Ising cells, L >= 4096): the tiles also give B, M, the counts, the sigma-h
-// histogram and the T bits (tile_bmq) and the residue rows of the sampled
-// rows after the T bits (tile_residues), so the B/M/Q pass need not read the
-// lattice again and the sampled x pass reads packed rows; acc[14] counts the
-// workgroups that saw a cell holding no spin, for which the caller runs the
-// B/M/Q pass after all.
-template <int MODEL, bool FUSED>
-__global__ __launch_bounds__(256) void corr_short_kernel(const uint32_t* __restrict__ planes, uint32_t L, int R,
-                                                         int64_t* __restrict__ Cx, int64_t* __restrict__ Cy,
-                                                         int64_t* __restrict__ acc, uint32_t* __restrict__ tb)
-{
-    using TT = ShortTile<MODEL, FUSED>;
-    __shared__ TT T;
-    __shared__ int64_t red[4][66];
-    __shared__ int64_t red_bmq[4][15];
-    const uint32_t Wp = L >> 6;                     // tile words per row, every model
-    const uint32_t nstrips = (Wp + kSW - 1) / kSW;
-    const uint32_t ntiles = nstrips * (L / kTH);
-    const size_t plane_units = (size_t)L * Wp;      // 16-byte vectors (4-bit) or words (1-bit) per plane
-    const uint4* P4 = reinterpret_cast<const uint4*>(planes);
-    // thread: word column j; waves 0 and 2 take the x axis, waves 1 and 3 the
-    // y axis (uniform per wave); the two 32-lane halves of a wave and the
-    // wave pair give the row group g, rows G g .. G g + G - 1 of the tile
-    // (G = kTH / 4)
-    const int j = threadIdx.x & (kSW - 1);
-    const int wave = threadIdx.x >> 6;
-    const int axis = wave & 1;
-    const int g = ((wave >> 1) << 1) | ((threadIdx.x >> 5) & 1);
-    int cacc[33];
-#pragma unroll
-    for (int k = 0; k < 33; ++k) cacc[k] = 0;
-    int64_t pairs = 0;
-    uint32_t bad = 0, np1 = 0, sites = 0;
-    uint32_t hist[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) hist[k] = 0;
-    // each workgroup takes a contiguous run of tiles, strip by strip and top
-    // to bottom within a strip, so a tile's 32 halo rows are the next tile's
-    // source rows: they move up in LDS and only 32 new rows are loaded
-    const uint32_t RT = L / kTH;                    // row tiles per strip
-    const uint32_t t_begin = (uint32_t)((uint64_t)blockIdx.x * ntiles / gridDim.x);
-    const uint32_t t_end = (uint32_t)((uint64_t)(blockIdx.x + 1) * ntiles / gridDim.x);
-    constexpr uint32_t NB = TT::NB;
-    constexpr uint32_t COLS = TT::COLS, CO = TT::CO;
-    for (uint32_t tile = t_begin; tile < t_end; ++tile) {
-        const uint32_t strip = tile / RT;
-        const uint32_t rt = tile - strip * RT;
-        const uint32_t q0 = strip * kSW;
-        const uint32_t y0 = rt * kTH;
-        const bool reuse = tile != t_begin && rt != 0;
-        __syncthreads();
-        if (reuse) {
-            // rows kTH .. kTH + kHalo - 1 become rows 0 .. kHalo - 1, one
-            // (plane, bit plane) block of kTileRows x COLS words at a time
-#pragma unroll
-            for (uint32_t blk = 0; blk < 2 * NB; ++blk) {
-                uint32_t* base = &T.v[blk / NB][blk % NB][0][0];
-                for (uint32_t o = threadIdx.x; o < kHalo * COLS; o += blockDim.x)
-                    base[o] = base[o + kTH * COLS];
-            }
-            __syncthreads();
-        }
-        const uint32_t row0 = reuse ? (uint32_t)kHalo : 0u;
-        // the new rows: lane (column lc, row group lg) takes column lc of rows
-        // row0 + lg, row0 + lg + 8, ...; then one thread per row each halo
-        // column (the word right of the strip and, fused, the last cell of
-        // the word left of it, periodic in the row)
-        const uint32_t lc = threadIdx.x & (kSW - 1), lg = threadIdx.x >> 5;
-        tile_load<MODEL>(T, planes, P4, plane_units, Wp, L, y0, row0 + lg, blockDim.x / kSW, lc + CO,
-                         wrap_col(q0 + lc, Wp), bad);
-        if (threadIdx.x < kTileRows - row0)
-            tile_load<MODEL>(T, planes, P4, plane_units, Wp, L, y0, row0 + threadIdx.x, kTileRows, kSW + CO,
-                             wrap_col(q0 + kSW, Wp), bad);
-        else if (FUSED && threadIdx.x >= 128 && threadIdx.x - 128 < kTileRows - row0)
-            tile_load_left(T, P4, plane_units, Wp, L, y0, row0 + threadIdx.x - 128, (q0 + Wp - 1) % Wp);
-        __syncthreads();
-        if (q0 + (uint32_t)j < Wp) {
-            if (axis == 0) short_tile<MODEL, 0>(T, j, g, R, cacc);
-            else short_tile<MODEL, 1>(T, j, g, R, cacc);
-            pairs += 16 * kTH;     // kTH / 4 rows x 2 planes x 32 cells, per distance
-        }
-        if constexpr (FUSED) {
-            tile_bmq<MODEL>(T, y0, q0, L, Wp, j, tb, hist, np1, sites);
-            if (tb) tile_residues(T, y0, q0, L, tb + (size_t)L * (L >> 9));
-        }
-    }
-    int64_t v[66];
-#pragma unroll
-    for (int k = 0; k < 33; ++k) {
-        const int64_t sk = k > R ? 0 : (MODEL != 1 ? pairs - 2 * (int64_t)cacc[k] : (int64_t)cacc[k]);
-        v[k] = axis == 0 ? sk : 0;
-        v[33 + k] = axis == 1 ? sk : 0;
-    }
-    block_add_xy<33>(v, Cx, Cy, red);
-    if (FUSED) {
-        // t = 4 (two aligned neighbours) is the rest; each bond is seen from
-        // both ends, so B = 2 N - sum of d over the sites (d = (8 - t) / 2)
-        hist[4] = sites - hist[0] - hist[2] - hist[6] - hist[8];
-        const int64_t dsum = (int64_t)hist[6] + 2 * (int64_t)hist[4] + 3 * (int64_t)hist[2] + 4 * (int64_t)hist[0];
-        int64_t w[15] = {2 * (int64_t)sites - dsum, 2 * (int64_t)np1 - (int64_t)sites, (int64_t)np1,
-                         (int64_t)sites - (int64_t)np1, 0};
-#pragma unroll
-        for (int k = 0; k < 9; ++k) w[5 + k] = (int64_t)hist[k];
-        w[14] = __syncthreads_or(bad != 0) && threadIdx.x == 0 ? 1 : 0;
-        block_add<15>(w, acc, red_bmq);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -847,12 +390,12 @@ __global__ __launch_bounds__(256) void corr_all_kernel(const uint32_t* __restric
 // ---------------------------------------------------------------------------
 // Correlations, sampled sources (x = y = 0 mod 16), as bits.
 //
-// T bits: for every row y, bit j of word k of row y (plane 0) is
-// [s(16 a, y) = +1] with a = 32 k + j, and for Blume-Capel plane 1 holds
-// [s(16 a, y) != 0]; a row has tbits_words(L) = max(1, L / 512) words, and
-// below L = 512 the NS = L / 16 bits of a row repeat to fill the word (NS
-// divides 32), so a rotation by m of the word is a shift by m mod NS.  The
-// site (16 a, y) has colour y & 1 and in-plane index 8 a.
+// T bits (layout in internal.h): for every row y, bit j of word k is
+// [s(16 a, y) = +1] with a = 32 k + j, and for Blume-Capel a second plane
+// holds [s(16 a, y) != 0]; below L = 512 the NS = L / 16 bits of a row repeat
+// to fill its one word (NS divides 32), so a rotation by m of the word is a
+// shift by m mod NS.  The site (16 a, y) has colour y & 1 and in-plane index
+// 8 a.
 //
 // A sum of s s' over the pairs of two such words is, with the mask z of the
 // pairs that count (both nonzero, and inside the row), popc(z) - 2
@@ -870,29 +413,27 @@ __device__ __forceinline__ int sampled_pairs(uint32_t s, uint32_t sz, uint32_t p
     return (int)popc(valid) - 2 * (int)popc(valid & (s ^ p));
 }
 
-// T bits of one row, any L: thread per output word (the bits of 32
-// sources, or of NS repeated).  Used below L = 512, where the B/M/Q pass
-// does not write them.
+// T bits below L = 512, where the measurement pass does not write them:
+// thread per row, whose NS bits fill one word.
 template <int MODEL>
 __global__ __launch_bounds__(256) void tbits_kernel(const uint32_t* __restrict__ planes, uint32_t L,
                                                     uint32_t* __restrict__ tb)
 {
     using C = Cell<MODEL == 2 ? 1 : 4>;
     const uint32_t W = L >> C::kWordShift, NS = L >> 4;
-    const uint32_t NSW = L >= 512 ? L >> 9 : 1u;
     const size_t plane_words = (size_t)L * W;
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < L * NSW; g += gridDim.x * blockDim.x) {
-        const uint32_t y = g / NSW, k = g - y * NSW;
-        const uint32_t* row = planes + (y & 1u) * plane_words + (size_t)y * W;
-        uint32_t sb = 0, zb = 0;
-        for (uint32_t j = 0; j < 32; ++j) {
-            const int s = C::spin(row, 8u * ((32u * k + j) % NS));
-            sb |= (s > 0 ? 1u : 0u) << j;
-            zb |= (s != 0 ? 1u : 0u) << j;
-        }
-        tb[g] = sb;
-        if (MODEL == 1) tb[(size_t)L * NSW + g] = zb;
+    const uint32_t y = blockIdx.x * blockDim.x + threadIdx.x;
+    if (y >= L) return;
+    const uint32_t* row = planes + (y & 1u) * plane_words + (size_t)y * W;
+    uint32_t sb = 0, zb = 0;
+    for (uint32_t j = 0; j < 32; ++j) {
+        const int s = C::spin(row, 8u * (j % NS));
+        sb |= (s > 0 ? 1u : 0u) << j;
+        zb |= (s != 0 ? 1u : 0u) << j;
     }
+    const uint32_t at = (y & 15u) * NS + (y >> 4);
+    tb[at] = sb;
+    if (MODEL == 1) tb[L + at] = zb;
 }
 
 // Along x, one sampled row y = 16 b at a time (persistent over rows).  The
@@ -961,27 +502,28 @@ __global__ __launch_bounds__(kSxThreads) void corr_sxb_kernel(const uint32_t* __
         ++rows_done;
         __syncthreads();
         if (MODEL == 0 && rb != nullptr) {
-            // the residue rows the fused short-distance tiles wrote: row 0 the
-            // sources (residue 0), rows 1 .. G the residues rho0 .., each
-            // stored twice; kSxU loads in flight per thread
-            const uint32_t* src = rb + (size_t)y * NSW;   // residue row 16 b + rho at src + rho NSW
-            const uint32_t total = (1 + G) * NSW;
+            // the residue rows the measurement pass wrote, 16 of them word by
+            // word: row 0 takes the sources (residue 0), rows 1 .. G the
+            // residues rho0 .., each stored twice; kSxU loads in flight per thread
+            const uint32_t* src = rb + (size_t)b * NSW * 16;
+            const uint32_t total = NSW * 16;
             for (uint32_t base = threadIdx.x; base < total; base += kSxU * blockDim.x) {
                 uint32_t v[kSxU];
 #pragma unroll
                 for (uint32_t u = 0; u < kSxU; ++u) {
                     const uint32_t t = base + u * blockDim.x;
-                    const uint32_t rr = t / NSW, w = t - rr * NSW;
-                    const uint32_t rho = rr == 0 ? 0u : rho0 + rr - 1;
-                    v[u] = t < total ? src[(size_t)rho * NSW + w] : 0u;
+                    v[u] = t < total ? src[t] : 0u;
                 }
 #pragma unroll
                 for (uint32_t u = 0; u < kSxU; ++u) {
                     const uint32_t t = base + u * blockDim.x;
-                    if (t < total) {
-                        const uint32_t rr = t / NSW, w = t - rr * NSW;
-                        R[rr * rowstride + w] = v[u];
-                        R[rr * rowstride + NSW + w] = v[u];
+                    if (t >= total) break;
+                    const uint32_t rho = t & 15u, w = t >> 4, slot = rho - rho0;
+                    if (rho == 0) R[w] = v[u];
+                    if (slot < G) {
+                        uint32_t* row = R + (1 + slot) * rowstride + w;
+                        row[0] = v[u];
+                        row[NSW] = v[u];
                     }
                 }
             }
@@ -1158,173 +700,131 @@ __global__ __launch_bounds__(kSxThreads) void corr_sxb_kernel(const uint32_t* __
 }
 
 // Along y: S_y(r) = sum over the sampled rows b and words k of the pairs of
-// T row 16 b and T row 16 b + r (mod L).  Thread per (source row, group of
-// WPT words: 4 from L = 2048 on, read as one 16-byte load), grid row per
-// chunk of 32 distances; a thread keeps the source words and the 32
-// distance sums in registers, the target words come from L2.  Ising rows
-// from L = 512 on have no invalid bits: the sum is then 32 per word minus
-// twice the count of differing bits, which is all the loop counts.
-constexpr int kYChunk = 32;
+// T row 16 b and T row 16 b + r (mod L).  With r = 16 q + rho the partner rows
+// are those of residue class rho from b + q on, which the T bits hold one
+// after the other for each word.  A workgroup takes one word k and one class:
+// its NS words go to LDS (the first half twice, so that b + q needs no wrap:
+// 48 KiB at L = 2^17), and a thread walks the source words b, kYGroup
+// distances of the class at a time, one LDS read, xor and bit count each,
+// neighbouring lanes reading neighbouring words.  Each word of the T bits is
+// read once as a partner, however many distances there are, and the kernel is
+// bound by the LDS reads.  4-bit Ising L = 2^17, 480 distances: 0.23 ms; with
+// the T bits row by row, partners read from the last-level cache, 0.43.  STAGED false: classes that do not fit LDS are read
+// from memory (L = 2^20, and Blume-Capel at L = 2^19).
+// DIFF (Ising from L = 512 on): no word has invalid bits, so the sum is 32 per
+// word minus twice the count of differing bits, which is all the loop counts.
+constexpr int kYGroup = 8;
+constexpr int kYUnroll = 4;
+constexpr int kYThreads = 256;
 
-template <int WPT>
-__device__ __forceinline__ void load_words(const uint32_t* __restrict__ p, uint32_t (&w)[WPT])
+// The source words b, b + kYThreads, .. (U of them) against kYGroup partners
+// at offsets q.
+template <int NB, bool STAGED, bool DIFF, int U>
+__device__ __forceinline__ void sy_rows(const uint32_t* src, size_t zoff, const uint32_t* part, size_t part_z,
+                                        uint32_t NS, uint32_t valid, uint32_t b, const uint32_t (&q)[kYGroup],
+                                        uint32_t (&acc)[kYGroup])
 {
-    if (WPT == 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        w[0] = v.x;
-        w[WPT > 1 ? 1 : 0] = v.y;
-        w[WPT > 2 ? 2 : 0] = v.z;
-        w[WPT > 3 ? 3 : 0] = v.w;
-    } else {
+    uint32_t s[U], sz[U];
 #pragma unroll
-        for (int i = 0; i < WPT; ++i) w[i] = p[i];
+    for (int u = 0; u < U; ++u) {
+        s[u] = src[b + u * kYThreads];
+        sz[u] = NB == 2 ? src[zoff + b + u * kYThreads] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kYGroup; ++j) {
+        const uint32_t* p = part + b + q[j];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t* at = STAGED ? p + u * kYThreads : part + ((b + q[j] + u * kYThreads) & (NS - 1));
+            if (DIFF)
+                acc[j] = bcnt_acc(s[u] ^ *at, acc[j]);
+            else
+                acc[j] += (uint32_t)sampled_pairs<NB == 2 ? 1 : 0>(s[u], sz[u], *at, NB == 2 ? at[part_z] : 0u, valid,
+                                                                   false);
+        }
     }
 }
 
-template <int MODEL, int WPT>
-__global__ __launch_bounds__(256) void corr_syb_kernel(const uint32_t* __restrict__ tb, uint32_t L,
-                                                       const int32_t* __restrict__ rlist, int nr,
-                                                       int64_t* __restrict__ Cy)
+template <int NB, bool STAGED, bool DIFF>
+__global__ __launch_bounds__(kYThreads) void corr_sy_kernel(const uint32_t* __restrict__ tb, uint32_t L,
+                                                            const int32_t* __restrict__ rlist, int nr,
+                                                            int64_t* __restrict__ Cy)
 {
-    constexpr int NB = MODEL == 1 ? 2 : 1;
+    extern __shared__ uint32_t cls[];                     // STAGED: [NB][NS + NS / 2]
+    __shared__ int s_index[kYGroup + kYThreads], s_shift[kYGroup + kYThreads];
+    __shared__ int s_n;
+    __shared__ uint32_t red[kYThreads / 64][kYGroup];
     const uint32_t NS = L >> 4;
     const uint32_t NSW = L >= 512 ? L >> 9 : 1u;
-    const uint32_t groups = NSW / WPT;                    // a power of two
-    const uint32_t g_log = 31 - __builtin_clz(groups);
-    const bool full = L >= 512;
-    const bool diff_only = MODEL != 1 && full;
-    const uint32_t valid = full ? 0xFFFFFFFFu : (NS >= 32 ? 0xFFFFFFFFu : ((1u << NS) - 1u));
+    const uint32_t valid = NS >= 32 ? 0xFFFFFFFFu : ((1u << NS) - 1u);
+    const uint32_t rho = blockIdx.x & 15u, k = blockIdx.x >> 4;
+    const uint32_t* src = tb + (size_t)k * L;             // class 0: the sources
+    const uint32_t* part = src + rho * NS;
     const size_t zoff = (size_t)L * NSW;                  // plane 1 (Blume-Capel nonzero bits)
-    const int k0 = blockIdx.y * kYChunk;
-    const int kn = min(kYChunk, nr - k0);
-    uint32_t rr[kYChunk];
-    int acc[kYChunk];
-#pragma unroll
-    for (int k = 0; k < kYChunk; ++k) {
-        rr[k] = k < kn ? (uint32_t)rlist[k0 + k] : 0u;
-        acc[k] = 0;
-    }
-    int words = 0;                                        // source words taken by this thread
-    const uint32_t pairs = NS * groups;
-    // workgroup ids go round-robin to the 8 XCDs: XCD x takes the x-th eighth
-    // of the source rows, so neighbouring source rows (whose partner rows at
-    // nearby distances coincide) meet in the same L2
-    const uint32_t nb = gridDim.x;
-    const uint32_t bx = (nb & 7u) == 0 ? (blockIdx.x & 7u) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    for (uint32_t p = bx * blockDim.x + threadIdx.x; p < pairs; p += gridDim.x * blockDim.x) {
-        const uint32_t b = p >> g_log, w = (p & (groups - 1)) * WPT;
-        const uint32_t y = 16 * b;
-        uint32_t s[WPT], sz[WPT];
-        load_words<WPT>(tb + (size_t)y * NSW + w, s);
-        if (NB == 2) load_words<WPT>(tb + zoff + (size_t)y * NSW + w, sz);
-        words += WPT;
-#pragma unroll
-        for (int k = 0; k < kYChunk; ++k) {
-            if (k < kn) {
-                const uint32_t yp = (y + rr[k]) & (L - 1);
-                uint32_t t[WPT], tz[WPT];
-                load_words<WPT>(tb + (size_t)yp * NSW + w, t);
-                if (NB == 2) load_words<WPT>(tb + zoff + (size_t)yp * NSW + w, tz);
-#pragma unroll
-                for (int i = 0; i < WPT; ++i) {
-                    if (diff_only)
-                        acc[k] += (int)popc(s[i] ^ t[i]);
-                    else
-                        acc[k] += sampled_pairs<MODEL>(s[i], NB == 2 ? sz[i] : 0u, t[i], NB == 2 ? tz[i] : 0u, valid,
-                                                       full);
-                }
-            }
+    const uint32_t len = NS + NS / 2;                     // r <= L / 2: q <= NS / 2
+    if (threadIdx.x == 0) s_n = 0;
+    if (STAGED)
+        for (uint32_t i = threadIdx.x; i < len; i += kYThreads) {
+            cls[i] = part[i & (NS - 1)];
+            if (NB == 2) cls[len + i] = part[zoff + (i & (NS - 1))];
         }
-    }
-    __shared__ int red[4][kYChunk];
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < kYChunk; ++k) {
-        const int v = diff_only ? 32 * words - 2 * acc[k] : acc[k];
-        const int s2 = wave_sum_i32(v);
-        if ((threadIdx.x & 63) == 0) red[wave][k] = s2;
-    }
     __syncthreads();
-    if ((int)threadIdx.x < kn) {
-        const int k = threadIdx.x;
-        const int64_t tot = (int64_t)red[0][k] + red[1][k] + red[2][k] + red[3][k];
-        if (tot != 0) atomicAdd((unsigned long long*)&Cy[k0 + k], (unsigned long long)tot);
-    }
-}
-
-// Along y, the sampled distances r0 .. r0 + nl - 1 that follow one another
-// (the protocol's linear range).  Source rows 16 b and 16 (b + 1) meet the
-// same partner rows at distances r + 16 and r, so a workgroup takes a band of
-// kYLRows source rows and stages their partner rows, 16 (kYLRows - 1) +
-// kYLDist consecutive T rows, in LDS, kYLWords words of each at a time (a
-// row of T words is a multiple of 8 from L = 4096 on; rows padded by one
-// vector); thread d owns distance r0 + kYLDist c + d (c the grid
-// row) and keeps its count in a register over the band and all columns.
-// Ising rows from L = 4096 on: no invalid bits, so a word's sum is 32 minus
-// twice its differing bits.
-constexpr int kYLRows = 16;
-constexpr int kYLDist = 256;
-constexpr int kYLWords = 8;
-constexpr int kYLVec = kYLWords / 4;                  // 16-byte vectors of a row's column
-constexpr int kYLTgt = 16 * (kYLRows - 1) + kYLDist;
-constexpr int kYLPad = kYLVec + 1;                    // 16-byte vectors per staged row
-
-__global__ __launch_bounds__(256) void corr_sylin_kernel(const uint32_t* __restrict__ tb, uint32_t L, uint32_t r0,
-                                                         int nl, int64_t* __restrict__ Cy)
-{
-    __shared__ uint4 tgt[kYLTgt * kYLPad];
-    __shared__ uint4 src[kYLRows * kYLVec];
-    const uint32_t NSW = L >> 9;
-    // bands in XCD-contiguous eighths (workgroup ids go round-robin to the
-    // XCDs), so neighbouring bands share their partner rows in one L2
-    const uint32_t nb = gridDim.x;
-    const uint32_t band = (nb & 7u) == 0 ? (blockIdx.x & 7u) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    const uint32_t b0 = band * kYLRows;
-    const int c = blockIdx.y;
-    const uint32_t ra = r0 + (uint32_t)c * kYLDist;
-    const int nd = min(kYLDist, nl - c * kYLDist);
-    const uint32_t nvec = (16 * (kYLRows - 1) + (uint32_t)nd) * kYLVec;
-    const int d = threadIdx.x;
-    uint32_t acc = 0;
-    for (uint32_t w0 = 0; w0 < NSW; w0 += kYLWords) {
-        __syncthreads();
-        // vector v: row v / kYLVec, words w0 + 4 (v % kYLVec) ..; 8 loads in flight
-        for (uint32_t base = threadIdx.x; base < nvec; base += 8 * blockDim.x) {
-            uint4 x[8];
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) {
-                const uint32_t v = base + u * blockDim.x;
-                const uint32_t y = (16 * b0 + ra + v / kYLVec) & (L - 1);
-                x[u] = v < nvec ? *reinterpret_cast<const uint4*>(tb + (size_t)y * NSW + w0 + 4 * (v % kYLVec))
-                                : make_uint4(0, 0, 0, 0);
+    for (int base = 0;;) {
+        // the next distances of the class: at least kYGroup of them, or the last
+        int n = s_n;
+        while (n < kYGroup && base < nr) {
+            const int i = base + (int)threadIdx.x;
+            const uint32_t r = i < nr ? (uint32_t)rlist[i] : 0u;
+            __syncthreads();                              // every thread has read s_n
+            if (i < nr && (r & 15u) == rho) {
+                const int at = atomicAdd(&s_n, 1);
+                s_index[at] = i;
+                s_shift[at] = (int)(r >> 4);
             }
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) {
-                const uint32_t v = base + u * blockDim.x;
-                if (v < nvec) tgt[(v / kYLVec) * kYLPad + v % kYLVec] = x[u];
-            }
+            base += kYThreads;
+            __syncthreads();
+            n = s_n;
         }
-        if (threadIdx.x < kYLRows * kYLVec) {
-            const uint32_t i = threadIdx.x / kYLVec, j = threadIdx.x % kYLVec;
-            src[threadIdx.x] = *reinterpret_cast<const uint4*>(tb + (size_t)(16 * (b0 + i)) * NSW + w0 + 4 * j);
+        if (n == 0) break;
+        // (past the last distance: the sources themselves, and no sum)
+        const int kn = min(n, kYGroup);
+        uint32_t q[kYGroup], acc[kYGroup];
+#pragma unroll
+        for (int j = 0; j < kYGroup; ++j) {
+            q[j] = (uint32_t)__builtin_amdgcn_readfirstlane(j < kn ? s_shift[j] : 0);
+            acc[j] = 0;
+        }
+        const uint32_t* from = STAGED ? cls : part;
+        const size_t from_z = STAGED ? len : zoff;
+        if (NS % (kYThreads * kYUnroll) == 0) {
+            for (uint32_t b = threadIdx.x; b < NS; b += kYThreads * kYUnroll)
+                sy_rows<NB, STAGED, DIFF, kYUnroll>(src, zoff, from, from_z, NS, valid, b, q, acc);
+        } else {
+            for (uint32_t b = threadIdx.x; b < NS; b += kYThreads)
+                sy_rows<NB, STAGED, DIFF, 1>(src, zoff, from, from_z, NS, valid, b, q, acc);
+        }
+#pragma unroll
+        for (int j = 0; j < kYGroup; ++j) {
+            const int v = wave_sum_i32((int)acc[j]);
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = (uint32_t)v;
         }
         __syncthreads();
-        if (d < nd) {
-            for (int i = 0; i < kYLRows; ++i) {
-#pragma unroll
-                for (int j = 0; j < kYLVec; ++j) {
-                    const uint4 a = src[i * kYLVec + j], t = tgt[(16 * i + d) * kYLPad + j];
-                    acc = bcnt_acc(a.x ^ t.x, acc);
-                    acc = bcnt_acc(a.y ^ t.y, acc);
-                    acc = bcnt_acc(a.z ^ t.z, acc);
-                    acc = bcnt_acc(a.w ^ t.w, acc);
-                }
-            }
+        if ((int)threadIdx.x < kn) {
+            int64_t v = 0;
+            for (int w = 0; w < kYThreads / 64; ++w) v += (int32_t)red[w][threadIdx.x];
+            if (DIFF) v = 32 * (int64_t)NS - 2 * v;
+            if (v != 0) atomicAdd((unsigned long long*)&Cy[s_index[threadIdx.x]], (unsigned long long)v);
         }
-    }
-    if (d < nd) {
-        const int64_t v = (int64_t)32 * kYLRows * NSW - 2 * (int64_t)acc;
-        atomicAdd((unsigned long long*)&Cy[c * kYLDist + d], (unsigned long long)v);
+        // the distances that follow the group move up
+        const bool rest = (int)threadIdx.x < n - kn;
+        const int index = rest ? s_index[kn + threadIdx.x] : 0, shift = rest ? s_shift[kn + threadIdx.x] : 0;
+        __syncthreads();
+        if (rest) {
+            s_index[threadIdx.x] = index;
+            s_shift[threadIdx.x] = shift;
+        }
+        if (threadIdx.x == 0) s_n = n - kn;
+        __syncthreads();
     }
 }
 
@@ -1344,20 +844,6 @@ hipError_t launch_zero(int64_t* p, int64_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-// Optional cap on the workgroups of the persistent measurement kernels
-// (B/M/Q pass, short-distance tiles, sampled x rows): the environment
-// variable MCL_MEASURE_GRID, read at every launch.  It changes how the work
-// is split over workgroups, never the sums; a test uses it to give each
-// workgroup several tasks, tiles and rows at small L.
-uint32_t grid_cap(uint32_t want)
-{
-    if (const char* e = std::getenv("MCL_MEASURE_GRID")) {
-        const long long v = std::atoll(e);
-        if (v > 0 && (uint64_t)v < want) return (uint32_t)v;
-    }
-    return want;
-}
-
 // Optional band height of the B/M/Q pass: MCL_MEASURE_ROWS (2 to 64, read
 // at every launch; the largest divisor of L up to it is taken).  Like the
 // grid cap it changes the split of the work only; a test uses it to run the
@@ -1371,7 +857,7 @@ int64_t bmq_rows(const Geom& g)
     return pick_rows(g.L, g.Q * (g.L / 64) >= (int64_t(1) << 20) ? 64 : 32);
 }
 
-hipError_t launch_bmq(const Geom& g, int model, int64_t* acc, uint32_t* tbits, hipStream_t s)
+hipError_t launch_bmq(const Geom& g, int model, int64_t* acc, hipStream_t s)
 {
     // one thread per task, bands of 64 rows while that leaves 2^20 tasks or
     // more (else 32).  The words beside a vector come from the neighbouring
@@ -1383,67 +869,43 @@ hipError_t launch_bmq(const Geom& g, int model, int64_t* acc, uint32_t* tbits, h
     // 2.06 - 2.09 ms each way once the halo loads were gone.
     const int64_t rows = bmq_rows(g);
     const int64_t threads = g.Q * (g.L / rows);
-    const uint32_t grid = grid_cap((uint32_t)((threads + 255) / 256));
+    const uint32_t grid = measure_grid_cap((uint32_t)((threads + 255) / 256));
     const uint32_t L = (uint32_t)g.L, R = (uint32_t)rows;
-    // the pass writes the T bits from L = 512 on; below, a kernel of its own
-    uint32_t* tb = g.L >= 512 ? tbits : nullptr;
     const bool wave_rows = (g.Q & 63) == 0;
     if (model == 2) {
         if (wave_rows)
-            hipLaunchKernelGGL((bmq_kernel<2, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<2, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
         else
-            hipLaunchKernelGGL((bmq_kernel<2, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<2, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
     } else if (model == 1) {
         if (wave_rows)
-            hipLaunchKernelGGL((bmq_kernel<1, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<1, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
         else
-            hipLaunchKernelGGL((bmq_kernel<1, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<1, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
     } else {
         if (wave_rows)
-            hipLaunchKernelGGL((bmq_kernel<0, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<0, true>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
         else
-            hipLaunchKernelGGL((bmq_kernel<0, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc, tb);
+            hipLaunchKernelGGL((bmq_kernel<0, false>), dim3(grid), dim3(256), 0, s, g.plane(0), g.plane(1), L, R, acc);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !tbits || tb) return e;
-    const uint32_t nw = (uint32_t)(g.L * tbits_words(g.L));
-    const dim3 tg((nw + 255) / 256);
-    if (model == 2)
-        hipLaunchKernelGGL(tbits_kernel<2>, tg, dim3(256), 0, s, g.plane0, L, tbits);
-    else if (model == 1)
-        hipLaunchKernelGGL(tbits_kernel<1>, tg, dim3(256), 0, s, g.plane0, L, tbits);
-    else
-        hipLaunchKernelGGL(tbits_kernel<0>, tg, dim3(256), 0, s, g.plane0, L, tbits);
     return hipGetLastError();
 }
 
-bool bmq_fused(const Geom& g, int model)
+hipError_t launch_tbits(const Geom& g, int model, uint32_t* tbits, hipStream_t s)
 {
-    if (model != 0 || g.L < 4096) return false;
+    if (g.L >= 512) return hipErrorInvalidValue;
+    const dim3 grid((uint32_t)((g.L + 255) / 256));
+    const uint32_t L = (uint32_t)g.L;
+    if (model == 2) hipLaunchKernelGGL(tbits_kernel<2>, grid, dim3(256), 0, s, g.plane0, L, tbits);
+    else if (model == 1) hipLaunchKernelGGL(tbits_kernel<1>, grid, dim3(256), 0, s, g.plane0, L, tbits);
+    else hipLaunchKernelGGL(tbits_kernel<0>, grid, dim3(256), 0, s, g.plane0, L, tbits);
+    return hipGetLastError();
+}
+
+bool bmq_fused()
+{
     if (const char* e = std::getenv("MCL_MEASURE_FUSED")) return std::atoi(e) != 0;
     return true;
-}
-
-hipError_t launch_corr_short(const Geom& g, int model, int R, int64_t* Cx, int64_t* Cy, int64_t* acc,
-                             uint32_t* tbits, hipStream_t s)
-{
-    if (R < 0) return hipSuccess;
-    const uint32_t Wp = (uint32_t)(g.L >> 6);
-    const uint32_t nstrips = (Wp + kSW - 1) / kSW;
-    const uint32_t ntiles = nstrips * (uint32_t)(g.L / kTH);
-    const dim3 grid(grid_cap(std::min<uint32_t>(ntiles, 1024)));
-    const uint32_t L = (uint32_t)g.L;
-    if (acc && (model != 0 || g.L < 4096 || (tbits && (Wp % kSW) != 0))) return hipErrorInvalidValue;
-    if (acc) {
-        hipLaunchKernelGGL((corr_short_kernel<0, true>), grid, dim3(256), 0, s, g.plane0, L, R, Cx, Cy, acc, tbits);
-    } else if (model == 0) {
-        hipLaunchKernelGGL((corr_short_kernel<0, false>), grid, dim3(256), 0, s, g.plane0, L, R, Cx, Cy, acc, tbits);
-    } else if (model == 1) {
-        hipLaunchKernelGGL((corr_short_kernel<1, false>), grid, dim3(256), 0, s, g.plane0, L, R, Cx, Cy, acc, tbits);
-    } else {
-        hipLaunchKernelGGL((corr_short_kernel<2, false>), grid, dim3(256), 0, s, g.plane0, L, R, Cx, Cy, acc, tbits);
-    }
-    return hipGetLastError();
 }
 
 hipError_t launch_corr_all(const Geom& g, const int32_t* r_dev, int nr, int64_t* Cx, int64_t* Cy, hipStream_t s)
@@ -1482,13 +944,13 @@ hipError_t corr_sampled_x(const Geom& g, const SampledArgs& a, hipStream_t s)
 {
     const uint32_t L = (uint32_t)g.L, NS = L / 16;
     if ((L & (L - 1)) != 0 || L < 64) return hipErrorInvalidValue;   // the protocol's lattices only
-    if (a.rbits && (MODEL != 0 || L < 4096)) return hipErrorInvalidValue;
+    if (a.rbits && (MODEL != 0 || L < 512)) return hipErrorInvalidValue;
     constexpr int NB = MODEL == 1 ? 2 : 1;
     // along x: LDS holds the source row and G residue rows of bits, each
     // row stored twice and padded by two words; a launch takes one distance
     // per thread
     const size_t rowb = ((size_t)NB * 2 * tbits_words(L) + 2) * 4, budget = sx_lds_budget();
-    const uint32_t gx = grid_cap(std::min<uint32_t>(NS, 1024));
+    const uint32_t gx = measure_grid_cap(std::min<uint32_t>(NS, 1024));
     uint32_t G = 16;
     while (G > 1 && rowb * (1 + G) > budget) G >>= 1;
     if (rowb * (1 + G) > budget) return hipErrorInvalidValue;
@@ -1513,34 +975,25 @@ hipError_t corr_sampled_x(const Geom& g, const SampledArgs& a, hipStream_t s)
     return hipSuccess;
 }
 
-template <int MODEL>
-hipError_t corr_sampled_y(const Geom& g, const SampledArgs& a, hipStream_t sy)
+hipError_t corr_sampled_y(const Geom& g, int model, const SampledArgs& a, hipStream_t s)
 {
     const uint32_t L = (uint32_t)g.L, NS = L / 16;
     if ((L & (L - 1)) != 0 || L < 64) return hipErrorInvalidValue;
-    // the consecutive distances first, for Ising from L = 4096 on: partner
-    // rows staged in LDS per band of source rows
-    int done = 0;
-    if (MODEL != 1 && L >= 4096 && a.nlin > 0) {
-        const dim3 gl(NS / kYLRows, (uint32_t)((a.nlin + kYLDist - 1) / kYLDist));
-        hipLaunchKernelGGL(corr_sylin_kernel, gl, dim3(kYLDist), 0, sy, a.tbits, L, a.rlin0, a.nlin, a.Cy);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        done = a.nlin;
-    }
-    const int nr = a.nr - done;
-    if (nr <= 0) return hipSuccess;
-    // the others: a group of 4 source-row words per thread from L = 2048 on
-    // (one word below), a grid row per 32 distances
-    const uint32_t wpt = tbits_words(L) >= 4 ? 4u : 1u;
-    const uint64_t groups = (uint64_t)NS * (tbits_words(L) / wpt);
-    const uint32_t gyx = grid_cap((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((groups + 255) / 256, 2048)));
-    const dim3 gy(gyx, (uint32_t)((nr + kYChunk - 1) / kYChunk));
-    if (wpt == 4)
-        hipLaunchKernelGGL((corr_syb_kernel<MODEL, 4>), gy, dim3(256), 0, sy, a.tbits, L, a.r + done, nr, a.Cy + done);
-    else
-        hipLaunchKernelGGL((corr_syb_kernel<MODEL, 1>), gy, dim3(256), 0, sy, a.tbits, L, a.r + done, nr, a.Cy + done);
-    return hipGetLastError();
+    const size_t need = (model == 1 ? 2 : 1) * (size_t)(NS + NS / 2) * 4;
+    const bool staged = need <= 152u * 1024u;             // with the kernel's own arrays, a workgroup's 160 KiB
+    const auto go = [&](auto kernel) {
+        if (staged && need > 32u * 1024u) {
+            const hipError_t e =
+                hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3(16u * (uint32_t)tbits_words(L)), dim3(kYThreads), staged ? need : 0, s, a.tbits, L,
+                           a.r, a.nr, a.Cy);
+        return hipGetLastError();
+    };
+    if (model == 1) return staged ? go(corr_sy_kernel<2, true, false>) : go(corr_sy_kernel<2, false, false>);
+    if (L < 512) return go(corr_sy_kernel<1, true, false>);
+    return staged ? go(corr_sy_kernel<1, true, true>) : go(corr_sy_kernel<1, false, true>);
 }
 
 }  // namespace
@@ -1554,7 +1007,7 @@ hipError_t launch_corr_sampled_x(const Geom& g, int model, const SampledArgs& a,
 hipError_t launch_corr_sampled_y(const Geom& g, int model, const SampledArgs& a, hipStream_t s)
 {
     if (a.nr <= 0) return hipSuccess;
-    return model == 2 ? corr_sampled_y<2>(g, a, s) : model == 1 ? corr_sampled_y<1>(g, a, s) : corr_sampled_y<0>(g, a, s);
+    return corr_sampled_y(g, model, a, s);
 }
 
 }  // namespace mcl
