@@ -1042,6 +1042,7 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
     // too, so the lattice is read once; cells that hold no spin set acc[14],
     // and then the B/M/Q pass runs after all (below)
     const bool fused = nr > 0 && mcl::bmq_fused();
+    const bool full = n_all - 1 > 32 && mcl::full_fits(h->L);
     if (!fused) MCL_HIP(mcl::launch_bmq(h->g, h->model, h->acc, h->stream));
     if (nr > 0) {
         // every-source distances are r = 0 .. n_all - 1 >= 32 (position j holds r = j)
@@ -1056,7 +1057,9 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
         sa.rbits = rbits;
         MCL_HIP(mcl::launch_pass(h->g, h->model, h->Cx, h->Cy, fused ? h->acc : nullptr,
                                  ns > 0 && big ? h->tbits : nullptr, rbits, h->stream));
-        if (n_all - 1 > 32)
+        if (full)
+            MCL_HIP(mcl::launch_corr_full(h->g, h->Cx, h->Cy, h->acc, h->stream));
+        else if (n_all - 1 > 32)
             MCL_HIP(mcl::launch_corr_all(h->g, h->rdev + 33, n_all - 33, h->Cx + 33, h->Cy + 33, h->stream));
         if (ns > 0) {
             if (!big) MCL_HIP(mcl::launch_tbits(h->g, h->model, h->tbits, h->stream));
@@ -1071,6 +1074,11 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
         MCL_HIP(hipMemcpyAsync(out->Cy, h->Cy, nr * sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
     }
     MCL_HIP(hipStreamSynchronize(h->stream));
+    if (full)
+        for (int j = 33; j < nr; ++j) {
+            out->Cx[j] += h->L * h->L - 2 * acc[15];
+            out->Cy[j] += h->L * h->L - 2 * acc[15];
+        }
     if (fused && acc[14] == 0) {
         // the pass counts #(+1), #(0) and the histogram of sigma h, whose sum is 2 B
         acc[3] = h->L * h->L - acc[2] - acc[4];

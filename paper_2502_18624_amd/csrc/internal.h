@@ -78,6 +78,12 @@ hipError_t launch_tbits(const Geom& g, int model, uint32_t* tbits, hipStream_t s
 // yes, unless the environment variable MCL_MEASURE_FUSED is 0 (read at every
 // call; a test compares the two).
 bool bmq_fused();
+// Correlations from every source at r = 33 .. L / 2 (Cx, Cy indexed by r):
+// adds 4 P(r), P the sum of (n / 2)(n' / 2) over the sources (cells with bit 0
+// set counted as n = 1), and sum n to acc[15], so that
+// C(r) = what was added - 2 acc[15] + L^2.  Lattices that full_fits() takes.
+bool full_fits(int64_t L);
+hipError_t launch_corr_full(const Geom& g, int64_t* Cx, int64_t* Cy, int64_t* acc, hipStream_t s);
 // Correlations from every source at distances r[0..nr) (any r <= L/2).
 hipError_t launch_corr_all(const Geom& g, const int32_t* r_dev, int nr, int64_t* Cx, int64_t* Cy,
                            hipStream_t s);

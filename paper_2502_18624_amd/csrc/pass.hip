@@ -42,20 +42,6 @@
 namespace mcl {
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-// c + a b^T for 16 rows each of a and b, 128 fp4 numbers a row: lane
-// (m = lane & 15, h = lane >> 4) holds numbers 32 h .. 32 h + 31 of row m, and
-// c[i] of lane (j, h) belongs to row 4 h + i of a and row j of b.
-__device__ __forceinline__ v4f mfma_f4(const uint4& a, const uint4& b, v4f c)
-{
-    const v8i va = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
-    const v8i vb = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(va, vb, c, 4, 4, 0, 0, 0, 0);
-}
-
 // Order of a wave's accesses to its own LDS words (they execute in order; the
 // compiler must not move a lane's read above another lane's write).
 __device__ __forceinline__ void wave_order()
@@ -87,33 +73,6 @@ struct Shape {
     // cell (0 .. 15) at nibble j of a staged block of 16 (the order of expand())
     static __device__ __forceinline__ int cell(int j) { return MODEL == 2 ? 4 * (j & 3) + (j >> 2) : j; }
 };
-
-// 32 one-bit cells as fp4 numbers 0 and 1 (bit 1 of a nibble), each block of
-// 16 cells in two words: cells 0, 4, 8, 12, 1, 5, 9, 13 and 2, 6, .., 15.
-__device__ __forceinline__ uint4 expand(uint32_t w)
-{
-    const uint32_t C = 0x22222222u;
-    const uint32_t e0 = (w << 1) & C, e1 = w & C, e2 = (w >> 1) & C, e3 = (w >> 2) & C;
-    return make_uint4(__builtin_amdgcn_perm(e1, e0, 0x05040100u), __builtin_amdgcn_perm(e3, e2, 0x05040100u),
-                      __builtin_amdgcn_perm(e1, e0, 0x07060302u), __builtin_amdgcn_perm(e3, e2, 0x07060302u));
-}
-
-// A 4-bit word with only the bits that define a spin: Ising bit 1 (s = +1
-// where set), Blume-Capel bit 0 (s = 0 where set), else bit 1.  `bad`
-// collects the bits of cells that hold no spin (Blume-Capel: bit 1 of `both`
-// too, set where bits 0 and 1 of a cell are).
-template <int MODEL>
-__device__ __forceinline__ uint32_t clean(uint32_t w, uint32_t& bad, uint32_t& both)
-{
-    if (MODEL == 0) {
-        bad |= w & 0xDDDDDDDDu;
-        return w & 0x22222222u;
-    }
-    const uint32_t up = w << 1;
-    bad |= w & 0xCCCCCCCCu;
-    both |= w & up;
-    return (w & ~up & 0x22222222u) | (w & 0x11111111u);
-}
 
 // Bit `BIT` of each nibble of a cleaned vector, cell 8 d + k at bit 4 k + d.
 template <int MODEL, int BIT>
@@ -469,11 +428,7 @@ __global__ __launch_bounds__(64 * Shape<MODEL>::WAVES) __attribute__((amdgpu_wav
                 // of the strip, its 32 rows of each: 128 rows in all
                 constexpr int BPH = S::NV / 2;
                 const auto column = [&](int p, int blk) {
-                    typedef __attribute__((address_space(3))) v2i* lp;
-                    char* a = strip_cells + (32 * p + m) * S::ROWB + 8 * (BPH * h + blk);
-                    const v2i r0 = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lp)a);
-                    const v2i r1 = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lp)(a + 16 * S::ROWB));
-                    return make_uint4((uint32_t)r0.x, (uint32_t)r0.y, (uint32_t)r1.x, (uint32_t)r1.y);
+                    return columns16(strip_cells + (32 * p + m) * S::ROWB + 8 * (BPH * h + blk), 16 * S::ROWB);
                 };
                 uint4 F0 = column(0, 0), F1 = column(1, 0);
 #pragma unroll

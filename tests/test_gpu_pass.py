@@ -77,3 +77,18 @@ def test_correlations_of_cells_that_hold_no_spin(mcl, model):
         s[y, 2 * np.arange(L // 2)[None, :] + ((y + c) & 1)] = spins[c]
     Cx, Cy, _ = oracle.corr(s, oracle.CORR_PROTOCOL, m["r"])
     assert np.array_equal(m["Cx"], Cx) and np.array_equal(m["Cy"], Cy)
+
+
+@pytest.mark.parametrize("model,L", [(0, 8960), (1, 9024), (2, 8960), (2, 9216)])
+def test_every_distance_at_the_limit_of_lds(mcl, model, L):
+    """FULL on both sides of the largest lattice whose rows fit LDS, a
+    distance list's ends and a few between against the oracle."""
+    print("full mode", model, L, flush=True)
+    lat = mcl.Lattice(model, L, 4960 + model)
+    m = lat.measure(mcl.CORR_FULL)
+    s = lat.read()
+    lat.free()
+    assert np.array_equal(m["r"], np.arange(L // 2 + 1))
+    r = np.array([0, 1, 32, 33, 34, 47, 48, 1000, 2049, L // 2 - 1, L // 2], dtype=np.int32)
+    Cx, Cy, _ = oracle.corr(s, oracle.CORR_FULL, r, 16)
+    assert np.array_equal(m["Cx"][r], Cx) and np.array_equal(m["Cy"][r], Cy)
