@@ -736,6 +736,80 @@ int sweep_checked(mcl_lattice* h, int64_t n, double beta, double D, bool allow_g
 }
 
 // ---------------------------------------------------------------------------
+// Pinned host memory of one call.  Taking it from the runtime costs more than
+// a small measurement, so up to kPinnedKept buffers of at most kPinnedMost
+// bytes wait for the next call of any handle and thread; others go back to the
+// runtime when their call ends.  A buffer is handed on only after the stream
+// that wrote it was waited for.
+// ---------------------------------------------------------------------------
+constexpr size_t kPinnedKept = 8, kPinnedMost = size_t(4) << 20;
+struct PinnedBuffer {
+    void* host = nullptr;
+    void* dev = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+};
+std::mutex g_pinned_mu;
+std::vector<PinnedBuffer> g_pinned;
+
+class Pinned {
+public:
+    explicit Pinned(hipStream_t s) : stream_(s) {}
+    Pinned(const Pinned&) = delete;
+    Pinned& operator=(const Pinned&) = delete;
+    hipError_t take(size_t bytes)
+    {
+        int device = 0;
+        hipError_t e = hipGetDevice(&device);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lk(g_pinned_mu);
+            for (size_t i = 0; i < g_pinned.size(); ++i)
+                if (g_pinned[i].bytes >= bytes && g_pinned[i].device == device) {
+                    b_ = g_pinned[i];
+                    g_pinned.erase(g_pinned.begin() + i);
+                    return hipSuccess;
+                }
+        }
+        PinnedBuffer b;
+        b.bytes = std::max<size_t>(bytes, 64 * 1024);
+        b.device = device;
+        e = hipHostMalloc(&b.host, b.bytes, hipHostMallocMapped);
+        if (e != hipSuccess) return e;
+        e = hipHostGetDevicePointer(&b.dev, b.host, 0);
+        if (e != hipSuccess) {
+            (void)hipHostFree(b.host);
+            return e;
+        }
+        b_ = b;
+        return hipSuccess;
+    }
+    ~Pinned()
+    {
+        if (!b_.host) return;
+        // (a call that returned early may have left kernels that write here)
+        const bool idle = hipStreamSynchronize(stream_) == hipSuccess;
+        if (idle && b_.bytes <= kPinnedMost) {
+            try {
+                std::lock_guard<std::mutex> lk(g_pinned_mu);
+                if (g_pinned.size() < kPinnedKept) {
+                    g_pinned.push_back(b_);
+                    return;
+                }
+            } catch (...) {
+            }
+        }
+        (void)hipHostFree(b_.host);
+    }
+    void* host() const { return b_.host; }
+    void* device() const { return b_.dev; }
+
+private:
+    hipStream_t stream_;
+    PinnedBuffer b_;
+};
+
+// ---------------------------------------------------------------------------
 // Argument checks and the lattices outside the batched launches, shared by
 // group_sweep and group_sweep_noalloc.
 // ---------------------------------------------------------------------------
@@ -1031,12 +1105,17 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
         out->n_r = 0;
     }
     const int nr = (int)r.size();
-    MCL_HIP(mcl::launch_zero(h->acc, mcl::kAccSlots, h->stream));
-    if (nr > 0) {
-        MCL_HIP(hipMemcpyAsync(h->rdev, r.data(), nr * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
-        MCL_HIP(mcl::launch_zero(h->Cx, nr, h->stream));
-        MCL_HIP(mcl::launch_zero(h->Cy, nr, h->stream));
-    }
+    // results and distances pass through pinned memory that the kernels
+    // address themselves: no copies, one wait
+    Pinned pin(h->stream);
+    MCL_HIP(pin.take((size_t)(mcl::kAccSlots + 2 * (size_t)nr) * 8 + (size_t)nr * 4));
+    int64_t* acc = (int64_t*)pin.host();
+    int64_t* host_Cx = acc + mcl::kAccSlots;
+    int64_t* host_Cy = host_Cx + nr;
+    if (nr > 0) std::memcpy(host_Cy + nr, r.data(), nr * sizeof(int32_t));
+    int64_t* dev_out = (int64_t*)pin.device();
+    MCL_HIP(mcl::launch_begin(h->acc, h->Cx, h->Cy, nr, h->rdev,
+                              nr > 0 ? (const int32_t*)(dev_out + mcl::kAccSlots + 2 * (int64_t)nr) : nullptr, h->stream));
     const int ns = nr - n_all;                          // sampled distances
     // with correlations, the measurement pass gives B, M, Q and the histogram
     // too, so the lattice is read once; cells that hold no spin set acc[14],
@@ -1067,13 +1146,12 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
             MCL_HIP(mcl::launch_corr_sampled_y(h->g, h->model, sa, h->stream));
         }
     }
-    int64_t acc[mcl::kAccSlots];
-    MCL_HIP(hipMemcpyAsync(acc, h->acc, sizeof(acc), hipMemcpyDeviceToHost, h->stream));
-    if (nr > 0) {
-        MCL_HIP(hipMemcpyAsync(out->Cx, h->Cx, nr * sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
-        MCL_HIP(hipMemcpyAsync(out->Cy, h->Cy, nr * sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
-    }
+    MCL_HIP(mcl::launch_finish(h->acc, h->Cx, h->Cy, nr, dev_out, h->stream));
     MCL_HIP(hipStreamSynchronize(h->stream));
+    if (nr > 0) {
+        std::memcpy(out->Cx, host_Cx, nr * sizeof(int64_t));
+        std::memcpy(out->Cy, host_Cy, nr * sizeof(int64_t));
+    }
     if (full)
         for (int j = 33; j < nr; ++j) {
             out->Cx[j] += h->L * h->L - 2 * acc[15];
@@ -1086,9 +1164,9 @@ int measure(mcl_lattice* h, int corr_mode, mcl_measure_out* out)
         for (int k = 0; k < 9; ++k) acc[0] += (k - 4) * acc[5 + k];
         acc[0] /= 2;
     } else if (fused) {
-        MCL_HIP(mcl::launch_zero(h->acc, mcl::kAccSlots, h->stream));
+        MCL_HIP(mcl::launch_begin(h->acc, h->Cx, h->Cy, 0, h->rdev, nullptr, h->stream));
         MCL_HIP(mcl::launch_bmq(h->g, h->model, h->acc, h->stream));
-        MCL_HIP(hipMemcpyAsync(acc, h->acc, sizeof(acc), hipMemcpyDeviceToHost, h->stream));
+        MCL_HIP(mcl::launch_finish(h->acc, h->Cx, h->Cy, 0, dev_out, h->stream));
         MCL_HIP(hipStreamSynchronize(h->stream));
     }
     out->B = acc[0];

@@ -46,10 +46,15 @@ hipError_t launch_set_word(uint32_t* p, uint32_t v, bool add, hipStream_t s);
 
 // Measurement kernels accumulating into int64 device scratch.
 // acc layout: [0] B, [1] M (from +1 count minus -1 count), [2] #(+1),
-// [3] #(-1), [4] #(0), [5..15] reserved; cells that are none of the three
-// (corrupted) are L^2 minus the three counts.
+// [3] #(-1), [4] #(0), [5..13] the sigma-h histogram, [14], [15] below; cells
+// that are none of the three (corrupted) are L^2 minus the three counts.
 constexpr int kAccSlots = 16;
-hipError_t launch_zero(int64_t* p, int64_t n, hipStream_t s);
+// Before the kernels of a measurement: acc and the nr sums of Cx and Cy to
+// zero, and (host_r set) the nr distances from pinned host memory to rdev.
+hipError_t launch_begin(int64_t* acc, int64_t* Cx, int64_t* Cy, int nr, int32_t* rdev, const int32_t* host_r,
+                        hipStream_t s);
+// After them: acc, Cx and Cy, one after the other, to pinned host memory.
+hipError_t launch_finish(const int64_t* acc, const int64_t* Cx, const int64_t* Cy, int nr, int64_t* host, hipStream_t s);
 // T bits of the sampled columns x = 0 mod 16: for every row y, bit j of its
 // word k is [s(16 (32 k + j), y) = +1] (and, Blume-Capel only, a second
 // plane of [s != 0] after the first); tbits_words(L) words per row, the L / 16

@@ -26,10 +26,28 @@
 namespace mcl {
 namespace {
 
-__global__ void zero_kernel(int64_t* p, int64_t n)
+__global__ __launch_bounds__(256) void begin_kernel(int64_t* __restrict__ acc, int64_t* __restrict__ Cx,
+                                                    int64_t* __restrict__ Cy, int nr, int32_t* __restrict__ rdev,
+                                                    const int32_t* __restrict__ host_r)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kAccSlots) acc[i] = 0;
+    if (i < nr) {
+        Cx[i] = Cy[i] = 0;
+        if (host_r) rdev[i] = host_r[i];
+    }
+}
+
+__global__ __launch_bounds__(256) void finish_kernel(const int64_t* __restrict__ acc, const int64_t* __restrict__ Cx,
+                                                     const int64_t* __restrict__ Cy, int nr,
+                                                     int64_t* __restrict__ host)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kAccSlots) host[i] = acc[i];
+    if (i < nr) {
+        host[kAccSlots + i] = Cx[i];
+        host[kAccSlots + nr + i] = Cy[i];
+    }
 }
 
 __device__ __forceinline__ uint32_t wrap(uint32_t v, uint32_t n) { return v >= n ? v - n : v; }
@@ -837,10 +855,18 @@ int64_t pick_rows(int64_t L, int64_t want)
 
 }  // namespace
 
-hipError_t launch_zero(int64_t* p, int64_t n, hipStream_t s)
+hipError_t launch_begin(int64_t* acc, int64_t* Cx, int64_t* Cy, int nr, int32_t* rdev, const int32_t* host_r,
+                        hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, p, n);
+    const dim3 grid((uint32_t)((std::max(nr, kAccSlots) + 255) / 256));
+    hipLaunchKernelGGL(begin_kernel, grid, dim3(256), 0, s, acc, Cx, Cy, nr, rdev, host_r);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const int64_t* acc, const int64_t* Cx, const int64_t* Cy, int nr, int64_t* host, hipStream_t s)
+{
+    const dim3 grid((uint32_t)((std::max(nr, kAccSlots) + 255) / 256));
+    hipLaunchKernelGGL(finish_kernel, grid, dim3(256), 0, s, acc, Cx, Cy, nr, host);
     return hipGetLastError();
 }
 

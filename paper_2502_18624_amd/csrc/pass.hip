@@ -507,36 +507,37 @@ __global__ __launch_bounds__(64 * Shape<MODEL>::WAVES) __attribute__((amdgpu_wav
         int pairs = 0;                                          // vectors of U_0 and U_1 that the lane holds
 #pragma unroll
         for (int c = 0; c < NC; ++c) pairs += valid[c] ? 1 : 0;
-        const int64_t sites = (int64_t)pairs * 64 * 2 * (t1 - t0);
-        int64_t v[13];
-        v[0] = sites - 2 * (2 * (int64_t)n2 + n1);              // the -2 sum n + N of every distance
-        v[1] = n2;
-        v[2] = n1;
+        // the wave's sums (below 2^31: kMaxTiles tiles of 2^15 cells at most)
+        const int sites = wave_sum_i32(pairs * 128 * (int)(t1 - t0));
+        const int s2 = wave_sum_i32((int)n2), s1 = MODEL == 1 ? wave_sum_i32((int)n1) : 0;
+        int t[9];
         if (MODEL == 1) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) v[3 + k] = hist[k];
-            v[3 + 4] += n1;                                     // sigma = 0: t = 4
+            for (int k = 0; k < 9; ++k) t[k] = wave_sum_i32((int)hist[k]);
+            t[4] += s1;                                         // sigma = 0: t = 4
         } else {
-            const int64_t d3 = hist[3], d1 = hist[0] - d3, d2 = hist[1] - d3, d4 = hist[2];
-            v[3 + 8] = sites - d1 - d2 - d3 - d4;
-            v[3 + 6] = d1;
-            v[3 + 4] = d2;
-            v[3 + 2] = d3;
-            v[3 + 0] = d4;
-            v[3 + 1] = v[3 + 3] = v[3 + 5] = v[3 + 7] = 0;
-        }
-        v[12] = (bad | (both & 0x22222222u)) != 0;
+            int e[4];
 #pragma unroll
-        for (int k = 0; k < 13; ++k) {
-            const int64_t s = wave_sum(v[k]);
-            if (lane == 0 && s != 0) {
-                if (k == 0) {
-                    for (int r = 0; r < 66; ++r) atomicAdd(&sums[r], (unsigned long long)s);
-                } else {
-                    atomicAdd(&sums[65 + k], (unsigned long long)s);
-                }
-            }
+            for (int k = 0; k < 4; ++k) e[k] = wave_sum_i32((int)hist[k]);
+            t[6] = e[0] - e[3];                                 // 1, 2, 3, 4 neighbours differ
+            t[4] = e[1] - e[3];
+            t[2] = e[3];
+            t[0] = e[2];
+            t[8] = sites - t[6] - t[4] - t[2] - t[0];
+            t[1] = t[3] = t[5] = t[7] = 0;
         }
+        const int worst = __any((bad | (both & 0x22222222u)) != 0);
+        // every distance gets -2 sum n + N
+        const int64_t rest = (int64_t)sites - 2 * (2 * (int64_t)s2 + s1);
+        for (int i = lane; i < 66; i += 64) atomicAdd(&sums[i], (unsigned long long)rest);
+        int64_t v = 0;
+        if (lane == 0) v = s2;
+        if (lane == 1) v = s1;
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            if (lane == 2 + k) v = t[k];
+        if (lane == 11) v = worst;
+        if (v != 0) atomicAdd(&sums[66 + lane], (unsigned long long)v);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 78; i += blockDim.x) {
@@ -558,10 +559,12 @@ hipError_t launch_pass(const Geom& g, int model, int64_t* Cx, int64_t* Cy, int64
     const uint32_t waves = model == 2 ? 2 : 4;
     const uint32_t nstrips = (uint32_t)((g.Q + per * waves - 1) / (per * waves));
     const int64_t RT = g.L / kTileRows;
-    // two waves per SIMD of 256 CUs; runs of at least two tiles (a run reads
-    // one tile above it), and of no more than kMaxTiles
+    // two waves per SIMD of 256 CUs while there are tiles for them, and runs of
+    // no more than kMaxTiles.  (A run reads one tile above it: runs of two
+    // tiles read half as much more, of one twice, but a small lattice is in
+    // cache and waits for its longest run.)
     const uint32_t cap = measure_grid_cap(2048 / waves);
-    int64_t runs = std::max<int64_t>(1, std::min<int64_t>(cap / nstrips, RT / 2));
+    int64_t runs = std::max<int64_t>(1, std::min<int64_t>(cap / nstrips, RT));
     runs = std::max<int64_t>(runs, (RT + kMaxTiles - 1) / kMaxTiles);
     const dim3 grid(measure_grid_cap(nstrips * (uint32_t)runs));
     const auto go = [&](auto kernel) {

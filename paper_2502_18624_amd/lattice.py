@@ -144,13 +144,10 @@ class Lattice:
 
     def measure(self, corr: int = CORR_NONE) -> dict:
         out = MeasureOut()
-        cap = 0
-        if corr != CORR_NONE:
-            cap = len(rset(corr, self.L, self.t))
-        r = np.zeros(max(cap, 1), dtype=np.int32)
-        cx = np.zeros(max(cap, 1), dtype=np.int64)
-        cy = np.zeros(max(cap, 1), dtype=np.int64)
-        ns = np.zeros(max(cap, 1), dtype=np.int64)
+        # room for every distance (0 .. L / 2), of which a mode may take fewer
+        cap = self.L // 2 + 1 if corr != CORR_NONE else 1
+        r = np.empty(cap, dtype=np.int32)
+        cx, cy, ns = (np.empty(cap, dtype=np.int64) for _ in range(3))
         out.r = r.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
         out.Cx = cx.ctypes.data_as(ctypes.POINTER(ctypes.c_int64))
         out.Cy = cy.ctypes.data_as(ctypes.POINTER(ctypes.c_int64))
