@@ -129,13 +129,15 @@ int lattice_init(mcl_lattice** out, int model, int64_t L, uint64_t seed, int ini
  * two other values, chosen by the proposal bit (0: next value cyclically in
  * -1,0,+1; 1: the one after), accepted by Metropolis on eq. (BC).
  * Asynchronous on the handle's stream; advances t by n.
- * Lattices of up to 2^24 cells run calls of 32 sweeps or more as replays of
+ * The smallest lattices (L <= 128, <= 256 from 4 sweeps on, 1-bit cells <= 512)
+ * are held in one workgroup's LDS for all sweeps of the call, one launch.
+ * Others of up to 2^24 cells run calls of 32 sweeps or more as replays of
  * an executable HIP graph of 32 sweeps, captured on first use for each
  * (beta, D) (up to four per handle, destroyed by lattice_free) on a
  * library stream of default priority; the sweep index then comes from a
  * word of the handle's device buffer.  The lattices are the same either
- * way.  The environment variable MCL_SWEEP_GRAPH=0 (never) or 1 (at any
- * size) overrides the size rule; it is read on each call.  While the
+ * way.  The environment variable MCL_SWEEP_GRAPH=0 (plain launches only) or
+ * 1 (replays at any size) overrides both size rules; it is read on each call.  While the
  * caller captures the handle's stream into a graph of its own, sweep()
  * queues plain launches, which carry absolute sweep indices: each replay of
  * the caller's graph repeats the same t values (t advances once, when the
@@ -208,7 +210,8 @@ int lattice_info(const mcl_lattice* h, int* model, int64_t* L, uint64_t* seed, i
  * sweep together.  Every lattice of L <= 2^17 with n[i] > 0 goes into one
  * launch per colour per sweep that covers all of them, all three models
  * alike (or, with the split_models tuning, one launch per model and
- * colour): a persistent grid walks a list of tiles of 256 threads, each
+ * colour; many small lattices, or a call of nothing else, are first run in
+ * LDS, a workgroup each, in one launch for all their sweeps): a persistent grid walks a list of tiles of 256 threads, each
  * tile one band of rows of one replica, so a replica's parameters are
  * wave-uniform.  Larger lattices fill the GPU alone and are swept one per
  * launch within the call.  All lattices must use the stream of hs[0], and
@@ -254,7 +257,8 @@ int group_sweep_noalloc(mcl_lattice* const* hs, int count, const int64_t* n,
 /* Tuning of group_sweep, process-wide; chosen by the package's autotuner.
  * Results never depend on it.
  *   rows_log2L[k] : band height (rows per thread: 8, 16, 32 or 64) for
- *                   lattices with 2^k <= L < 2^(k+1);
+ *                   lattices with 2^k <= L < 2^(k+1); a call with little
+ *                   work for the chip takes shorter bands;
  *   use_graph     : replay repeated call shapes from captured graphs;
  *   largest_first : order each launch's tile list by decreasing L (else
  *                   call order);

@@ -301,8 +301,12 @@ struct GroupLaunch {
     uint32_t grid;     // workgroups (a multiple of 8)
 };
 struct GroupImage {
-    GroupLaunch launches[3];   // one per model, or one for all
+    GroupLaunch launches[3];   // batched: one per model, or one for all
     int nlaunch = 0;
+    // resident replicas: descriptors [0, nres), 1-bit records [0, res_lut)
+    int nres = 0;
+    size_t res_lds = 0, res_lut = 0;
+    int64_t res_vectors = 0, res_nmax = 0;
     size_t ndesc = 0, nbc = 0, nlut = 0;
     size_t off_bc = 0, off_lut = 0, off_s = 0, bytes = 0;
     int64_t nmax = 0;
@@ -310,6 +314,67 @@ struct GroupImage {
 
 // Replicas of the batched launches: n > 0 and L <= kGroupMaxL.
 bool batched(const mcl_lattice* h, int64_t n) { return n > 0 && h->L <= kGroupMaxL; }
+
+// Lattices that a workgroup holds in LDS for all sweeps of a call (one compute
+// unit each).  Measured against launches per half-sweep, us per sweep at 64
+// sweeps (at one sweep), Ising / Blume-Capel: L = 128 2.6 (4.8) / 4.5 (7.2)
+// against 7.4 (7.8) / 11.3 (11.8); L = 256 7.4 (10.1) / 9.8 (13.1) against 8.1
+// (8.4) / 11.8 (12.7); L = 320 14.4 / 18.8 against 8.7 / 12.4.  1-bit cells:
+// L = 256 7.7 (23.8) against 18.8 (22.6), L = 512 16.2 (23.4) against 22.8 (26.5),
+// L = 768 35 against 23.
+bool resident_alone(const mcl_lattice* h, int64_t n)
+{
+    if (h->model == MCL_ISING_LUT) return h->L <= 512 && (n > 1 || h->L > 256);
+    return h->L <= 128 || (h->L <= 256 && n >= 4);
+}
+
+// In a batch: from kResidentMany replicas on that leave room for two of them
+// in a compute unit's LDS (L = 384, 1-bit L = 512), or where every replica of
+// the call would go that way alone.  They run before the batched launches, so
+// a few small replicas beside large ones are better off in those.  16 sweeps:
+// 128 of L = 256 195 against 325 us, 512 384 against 578, 256 of L = 384 402
+// against 651; 512 of L = 512, one to a compute unit, 1281 against 1450, but 128
+// of them 637 against 548.
+constexpr int kResidentMany = 128;
+constexpr size_t kResidentGroupLds = 76 * 1024;
+bool resident_in_group(const mcl_lattice* h)
+{
+    return mcl::resident_lds(h->model, h->L) <= kResidentGroupLds;
+}
+
+// Sweeps of one resident launch (about 2 ms at L = 256).
+constexpr int64_t kResidentSweeps = 256;
+
+// Band height of a replica: the tuning's for its size, halved `shift` times
+// and as often as it takes to fill a tile of 256 threads, but at least 2 rows.
+// A call whose replicas give few threads needs the shorter bands as a single
+// small lattice does (band_rows in sweep.hip): until there are kGroupThreads,
+// four rounds of workgroups at the four waves per SIMD of the mixed kernels,
+// a launch waits for its last, partly filled round.  48 replicas of L = 512 ..
+// 8192, 4 sweeps: 2.28 ms, against 2.41 at 2^19 threads, 2.85 with the tuning's
+// bands and 2.24 at 2^22, whose short bands read more halo rows.
+constexpr int64_t kGroupThreads = int64_t(1) << 20;
+int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int shift)
+{
+    int64_t rows = std::max<int64_t>(2, tun.rows_log2L[log2_floor(h->L)] >> shift);
+    while (rows > 2 && h->g.Q * (h->L / rows) < 256) rows >>= 1;
+    return rows;
+}
+
+// Descriptor of h for n sweeps, without its launch's fields and its tables.
+mcl::GroupDesc describe(const mcl_lattice* h, int64_t n)
+{
+    mcl::GroupDesc d;
+    std::memset(&d, 0, sizeof(d));
+    d.plane0 = h->g.plane0;
+    d.L = (uint32_t)h->L;
+    d.t0 = (uint32_t)h->t;
+    d.n = (uint32_t)n;
+    d.k0 = (uint32_t)h->seed;
+    d.k1 = (uint32_t)(h->seed >> 32);
+    d.model = (uint32_t)h->model;
+    return d;
+}
 
 // Plan the call (launches, tiles, grid) into `img`; when `host` is given,
 // also write the image there (it must hold img.bytes).  `order` is room for
@@ -319,13 +384,29 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
                  const mcl_group_tuning& tun, int cus, GroupImage& img, void* host, int* order)
 {
     img = GroupImage();
+    // which replicas go resident: every one that fits, if they are many; or all
+    // of a call's, if each is small enough to do so alone
+    int fit = 0, small = 0, all = 0;
     for (int i = 0; i < count; ++i)
         if (batched(hs[i], n[i])) {
-            img.nmax = std::max(img.nmax, n[i]);
+            ++all;
+            fit += resident_in_group(hs[i]);
+            small += resident_alone(hs[i], n[i]);
+        }
+    const bool res_many = fit >= kResidentMany, res_all = small == all;
+    const auto is_res = [&](int i) { return (res_many && resident_in_group(hs[i])) || res_all; };
+    int64_t threads_all = 0;
+    for (int i = 0; i < count; ++i)
+        if (batched(hs[i], n[i])) {
+            const bool res = is_res(i);
+            (res ? img.res_nmax : img.nmax) = std::max(res ? img.res_nmax : img.nmax, n[i]);
+            if (!res) threads_all += hs[i]->g.Q * (hs[i]->L / tun.rows_log2L[log2_floor(hs[i]->L)]);
             img.ndesc++;
             img.nbc += hs[i]->model == MCL_BC;
             img.nlut += hs[i]->model == MCL_ISING_LUT;
         }
+    int shift = 0;
+    while (shift < 5 && (threads_all << shift) < kGroupThreads) ++shift;
     img.off_bc = align_up(img.ndesc * sizeof(mcl::GroupDesc), 256);
     img.off_lut = align_up(img.off_bc + img.nbc * 96 * sizeof(uint2), 256);
     img.off_s = align_up(img.off_lut + img.nlut * sizeof(mcl::LutRec), 256);
@@ -337,13 +418,25 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
     uint32_t* htab = base ? (uint32_t*)(base + img.off_bc) : nullptr;
     mcl::LutRec* hlut = base ? (mcl::LutRec*)(base + img.off_lut) : nullptr;
     size_t k = 0, nb = 0, nl = 0;
-    for (int m = 0; m < (tun.split_models ? 3 : 1); ++m) {
+    // the resident replicas first, then the batched ones (model by model with
+    // split_models)
+    for (int pass = 0; pass < (tun.split_models ? 4 : 2); ++pass) {
+        const bool res = pass == 0;
+        const int m = !res && tun.split_models ? pass - 1 : -1;
         int cnt = 0;
         for (int i = 0; i < count; ++i)
-            if (batched(hs[i], n[i]) && (!tun.split_models || hs[i]->model == m)) order[cnt++] = i;
+            if (batched(hs[i], n[i]) && is_res(i) == res && (m < 0 || hs[i]->model == m)) order[cnt++] = i;
         if (cnt == 0) continue;
         // decreasing L, call order among equal L (an in-place sort on the pair)
-        if (tun.largest_first)
+        if (res)
+            // resident ones by cost, models together: workgroup ids go round
+            // the XCDs, which would otherwise divide alternating models
+            // among them
+            std::sort(order, order + cnt, [&](int a, int b) {
+                const auto key = [&](int i) { return std::make_tuple(-hs[i]->L, hs[i]->model != MCL_BC, hs[i]->model, i); };
+                return key(a) < key(b);
+            });
+        else if (tun.largest_first)
             std::sort(order, order + cnt,
                       [&](int a, int b) { return hs[a]->L != hs[b]->L ? hs[a]->L > hs[b]->L : a < b; });
         GroupLaunch ln{0, k, cnt, 0, 0};
@@ -351,21 +444,18 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         for (int j = 0; j < cnt; ++j) {
             const int i = order[j];
             const mcl_lattice* h = hs[i];
-            const uint32_t rows = (uint32_t)tun.rows_log2L[log2_floor(h->L)];
+            const uint32_t rows = (uint32_t)group_rows(h, tun, shift);
             const int64_t threads = h->g.Q * (h->L / rows);
             ln.mask |= h->model == MCL_ISING ? mcl::kMaskIsing : h->model == MCL_BC ? mcl::kMaskBC : mcl::kMaskLut;
+            if (res) {
+                img.res_lds = std::max(img.res_lds, mcl::resident_lds(h->model, h->L));
+                img.res_vectors = std::max(img.res_vectors, h->g.Q * h->L);
+                img.res_lut += h->model == MCL_ISING_LUT;
+            }
             if (base) {
-                mcl::GroupDesc d;
-                std::memset(&d, 0, sizeof(d));
-                d.plane0 = h->g.plane0;
-                d.L = (uint32_t)h->L;
+                mcl::GroupDesc d = describe(h, n[i]);
                 d.rows = rows;
-                d.t0 = (uint32_t)h->t;
-                d.n = (uint32_t)n[i];
-                d.k0 = (uint32_t)h->seed;
-                d.k1 = (uint32_t)(h->seed >> 32);
                 d.tile_begin = (uint32_t)tiles;
-                d.model = (uint32_t)h->model;
                 if (h->model == MCL_ISING) {
                     ising_thresholds(beta[i], d.T4, d.T8);
                 } else if (h->model == MCL_BC) {
@@ -387,6 +477,10 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
             nl += h->model == MCL_ISING_LUT;
             ++k;
             tiles += (uint64_t)((threads + 255) / 256);
+        }
+        if (res) {
+            img.nres = cnt;
+            continue;
         }
         if (tiles >= (uint64_t(1) << 32)) return MCL_ERANGE;
         ln.total = (uint32_t)tiles;
@@ -423,12 +517,35 @@ hipError_t group_launches(const GroupImage& img, const void* dev, int64_t s0, in
     return hipSuccess;
 }
 
+// The resident replicas' sweeps, the image on its way to `dev` on stream st.
+hipError_t group_resident(const GroupImage& img, const void* dev, hipStream_t st)
+{
+    const char* b = (const char*)dev;
+    for (int64_t s = 0; s < img.res_nmax; s += kResidentSweeps) {
+        const hipError_t e = mcl::launch_group_resident(
+            (const mcl::GroupDesc*)b, img.nres, img.res_lds, img.res_vectors, (uint32_t)s,
+            (uint32_t)std::min(s + kResidentSweeps, img.res_nmax), (const uint2*)(b + img.off_bc),
+            (const mcl::LutRec*)(b + img.off_lut), st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Bucket tables of the batched 1-bit replicas, whose records follow the
+// resident ones'.
+hipError_t group_buckets(const GroupImage& img, const void* dev, hipStream_t st)
+{
+    return mcl::launch_group_lut_buckets((const mcl::LutRec*)((const char*)dev + img.off_lut) + img.res_lut,
+                                         (int)(img.nlut - img.res_lut), st);
+}
+
 // Work of a planned call whose image is already on its way to `dev` on
-// stream st: the 1-bit bucket tables, then the sweeps as plain launches.
+// stream st: the resident replicas, the 1-bit bucket tables, then the sweeps
+// as plain launches.
 hipError_t group_plain(const GroupImage& img, const void* dev, hipStream_t st)
 {
-    hipError_t e = mcl::launch_group_lut_buckets((const mcl::LutRec*)((const char*)dev + img.off_lut), (int)img.nlut,
-                                                 st);
+    hipError_t e = group_resident(img, dev, st);
+    if (e == hipSuccess) e = group_buckets(img, dev, st);
     if (e != hipSuccess) return e;
     return group_launches(img, dev, 0, img.nmax, nullptr, st);
 }
@@ -523,7 +640,7 @@ int group_run(mcl_lattice* const* hs, int count, const int64_t* n, const double*
     std::vector<int> order((size_t)count);
     int rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, nullptr, order.data());
     if (rc) return rc;
-    if (img.nmax == 0) return MCL_OK;
+    if (img.nmax == 0 && img.res_nmax == 0) return MCL_OK;
 
     DeviceSlots& ds = g_slots[devid];
     Slot& sl = ds.slot[ds.next];
@@ -576,8 +693,8 @@ int group_run(mcl_lattice* const* hs, int count, const int64_t* n, const double*
     if (!use_graph) {
         MCL_HIP(group_plain(img, sl.dev, stream));
     } else {
-        MCL_HIP(mcl::launch_group_lut_buckets((const mcl::LutRec*)((const char*)sl.dev + img.off_lut), (int)img.nlut,
-                                              stream));
+        MCL_HIP(group_resident(img, sl.dev, stream));
+        MCL_HIP(group_buckets(img, sl.dev, stream));
         hipStream_t gs = stream;
         CaptureStream* cs = nullptr;
         if (stream == nullptr) {
@@ -714,13 +831,23 @@ int sweep_checked(mcl_lattice* h, int64_t n, double beta, double D, bool allow_g
 {
     if (n == 0) return MCL_OK;
     SweepParams p{};
+    const bool resident = resident_alone(h, n) && !std::getenv("MCL_SWEEP_GRAPH");
     if (h->model == MCL_ISING_LUT) {
         p.tab = lut_device_table(beta);
-        MCL_HIP(mcl::launch_lut_buckets(p.tab, h->lutb, h->stream));
+        if (!resident) MCL_HIP(mcl::launch_lut_buckets(p.tab, h->lutb, h->stream));
     } else if (h->model == MCL_ISING) {
         ising_thresholds(beta, p.T4, p.T8);
     } else {
         bc_table(beta, D, p.tb);
+    }
+    if (resident) {
+        mcl::GroupDesc d = describe(h, n);
+        d.T4 = p.T4;
+        d.T8 = p.T8;
+        for (int64_t s = 0; s < n; s += kResidentSweeps, d.t0 += (uint32_t)kResidentSweeps)
+            MCL_HIP(mcl::launch_resident(d, (uint32_t)std::min(kResidentSweeps, n - s), p.tb, p.tab, h->stream));
+        h->t += n;
+        return MCL_OK;
     }
     int64_t done = 0;
     if (allow_graph && n >= kGraphSweeps && use_sweep_graph(h)) {
@@ -910,7 +1037,7 @@ int group_run_noalloc(mcl_lattice* const* hs, int count, const int64_t* n, const
     GroupImage img;
     rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, nullptr, g_noalloc_order);
     if (rc) return rc;
-    if (img.nmax == 0) return MCL_OK;
+    if (img.nmax == 0 && img.res_nmax == 0) return MCL_OK;
     if (img.bytes > kNoAllocBytes) return MCL_ESCRATCH;
     // the host image is free once the copy of the last call (on any device) has run
     if (g_noalloc_last >= 0 && g_noalloc[g_noalloc_last].pending) {

@@ -150,6 +150,15 @@ constexpr int kMaskIsing = 1, kMaskBC = 2, kMaskLut = 4;
 hipError_t launch_group_half(int mask, int color, const GroupDesc* desc, int count, uint32_t total,
                              uint32_t grid, const uint2* bc_tables, const LutRec* luts, uint32_t s,
                              const uint32_t* sbase, uint32_t* ctr, hipStream_t st);
+// Lattices that a workgroup holds in LDS (resident_lds bytes of it: both
+// planes, and the bucket table of 1-bit cells), in one launch: n sweeps of a
+// single lattice with its tables by value, or sweeps [s0, min(s1, n)) of
+// `count` descriptors of any models, at most `lds` bytes and `vectors` 16-byte
+// vectors of a plane each.
+size_t resident_lds(int model, int64_t L);
+hipError_t launch_resident(const GroupDesc& d, uint32_t n, const BCTable& bc, const LutTable& lt, hipStream_t s);
+hipError_t launch_group_resident(const GroupDesc* desc, int count, size_t lds, int64_t vectors, uint32_t s0, uint32_t s1,
+                                 const uint2* bc_tables, const LutRec* luts, hipStream_t s);
 // Bucket tables of the 1-bit replicas of a batched call.
 hipError_t launch_group_lut_buckets(const LutRec* luts, int n, hipStream_t st);
 

@@ -440,14 +440,18 @@ __device__ __forceinline__ uint32_t lut_lookup(const uint32_t* __restrict__ T, u
 }
 
 // Random bits of 32 cells (8 groups of 4) from the 8 draws of two Philox
-// blocks P, R, by the exact table search.
-__device__ __forceinline__ uint32_t lut_word(const Philox4& P, const Philox4& R, const uint32_t* __restrict__ T,
-                                             uint32_t T8, uint32_t kmax)
+// blocks P, R, by the exact table search (a loop: it is seldom run, and
+// unrolled at every use it was half of the kernels' code).
+__device__ __forceinline__ uint32_t lut_word(Philox4 P, Philox4 R, const uint32_t* __restrict__ T, uint32_t T8,
+                                             uint32_t kmax)
 {
     uint32_t w = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        w |= lut_lookup(T, T8, kmax, philox_word(j < 4 ? P : R, j & 3)) << (4 * j);
+#pragma unroll 1
+    for (int j = 0; j < 8; ++j) {
+        w = (w >> 4) | (lut_lookup(T, T8, kmax, P.v0) << 28);
+        P = Philox4{P.v1, P.v2, P.v3, R.v0};
+        R = Philox4{R.v1, R.v2, R.v3, 0u};
+    }
     return w;
 }
 
