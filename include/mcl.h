@@ -129,15 +129,16 @@ int lattice_init(mcl_lattice** out, int model, int64_t L, uint64_t seed, int ini
  * two other values, chosen by the proposal bit (0: next value cyclically in
  * -1,0,+1; 1: the one after), accepted by Metropolis on eq. (BC).
  * Asynchronous on the handle's stream; advances t by n.
- * The smallest lattices (L <= 128, <= 256 from 4 sweeps on, 1-bit cells <= 512)
- * are held in one workgroup's LDS for all sweeps of the call, one launch.
- * Others of up to 2^24 cells run calls of 32 sweeps or more as replays of
- * an executable HIP graph of 32 sweeps, captured on first use for each
- * (beta, D) (up to four per handle, destroyed by lattice_free) on a
- * library stream of default priority; the sweep index then comes from a
- * word of the handle's device buffer.  The lattices are the same either
- * way.  The environment variable MCL_SWEEP_GRAPH=0 (plain launches only) or
- * 1 (replays at any size) overrides both size rules; it is read on each call.  While the
+ * Small lattices take fewer launches than one per half-sweep: the smallest
+ * (L <= 128, 1-bit cells 256) are held in one workgroup's LDS for the whole
+ * call, others (up to L = 7168, 1-bit cells 12288) run two to four sweeps in
+ * each pair of launches.  The environment variable MCL_SWEEP_GRAPH, read on
+ * each call, replaces that by one launch per half-sweep (0), or by replays of
+ * an executable HIP graph of 32 sweeps of such launches in calls of 32 sweeps
+ * or more, at any size (1); a graph is captured on first use for each (beta, D)
+ * (up to four per handle, destroyed by lattice_free) on a library stream of
+ * default priority, and the sweep index then comes from a word of the handle's
+ * device buffer.  The lattices are the same either way.  While the
  * caller captures the handle's stream into a graph of its own, sweep()
  * queues plain launches, which carry absolute sweep indices: each replay of
  * the caller's graph repeats the same t values (t advances once, when the

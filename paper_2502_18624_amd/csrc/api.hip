@@ -315,28 +315,36 @@ struct GroupImage {
 // Replicas of the batched launches: n > 0 and L <= kGroupMaxL.
 bool batched(const mcl_lattice* h, int64_t n) { return n > 0 && h->L <= kGroupMaxL; }
 
+// Whether a call has one such replica, which is then swept on its own.
+bool solo(mcl_lattice* const* hs, int count, const int64_t* n)
+{
+    int some = 0;
+    for (int i = 0; i < count; ++i) some += batched(hs[i], n[i]);
+    return some == 1;
+}
+
 // Lattices that a workgroup holds in LDS for all sweeps of a call (one compute
-// unit each).  Measured against launches per half-sweep, us per sweep at 64
-// sweeps (at one sweep), Ising / Blume-Capel: L = 128 2.6 (4.8) / 4.5 (7.2)
-// against 7.4 (7.8) / 11.3 (11.8); L = 256 7.4 (10.1) / 9.8 (13.1) against 8.1
-// (8.4) / 11.8 (12.7); L = 320 14.4 / 18.8 against 8.7 / 12.4.  1-bit cells:
-// L = 256 7.7 (23.8) against 18.8 (22.6), L = 512 16.2 (23.4) against 22.8 (26.5),
-// L = 768 35 against 23.
+// unit each).  us per sweep at 64 sweeps (at one), Ising / Blume-Capel, against
+// pairs of launches for several sweeps (and one launch per half-sweep): L = 128
+// 2.6 (4.6) / 3.7 (6.7) against 3.5 (7.8) / 5.0 (11.8); L = 192 5.6 / 7.3
+// against 3.6 / 4.9.  1-bit cells: L = 256 4.9 against 7.9, at one sweep 23.8
+// against 22.6.
 bool resident_alone(const mcl_lattice* h, int64_t n)
 {
-    if (h->model == MCL_ISING_LUT) return h->L <= 512 && (n > 1 || h->L > 256);
-    return h->L <= 128 || (h->L <= 256 && n >= 4);
+    if (h->model == MCL_ISING_LUT) return h->L <= 256 && n > 1;
+    return h->L <= 128;
 }
 
 // In a batch: from kResidentMany replicas on that leave room for two of them
 // in a compute unit's LDS (L = 384, 1-bit L = 512), or where every replica of
-// the call would go that way alone.  They run before the batched launches, so
+// the call is of L <= 256 (1-bit 512).  They run before the batched launches, so
 // a few small replicas beside large ones are better off in those.  16 sweeps:
-// 128 of L = 256 195 against 325 us, 512 384 against 578, 256 of L = 384 402
+// 64 of L = 256 184 against 311 us, 512 343 against 578, 256 of L = 384 402
 // against 651; 512 of L = 512, one to a compute unit, 1281 against 1450, but 128
 // of them 637 against 548.
 constexpr int kResidentMany = 128;
 constexpr size_t kResidentGroupLds = 76 * 1024;
+bool resident_small(const mcl_lattice* h) { return h->L <= (h->model == MCL_ISING_LUT ? 512 : 256); }
 bool resident_in_group(const mcl_lattice* h)
 {
     return mcl::resident_lds(h->model, h->L) <= kResidentGroupLds;
@@ -391,7 +399,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         if (batched(hs[i], n[i])) {
             ++all;
             fit += resident_in_group(hs[i]);
-            small += resident_alone(hs[i], n[i]);
+            small += resident_small(hs[i]);
         }
     const bool res_many = fit >= kResidentMany, res_all = small == all;
     const auto is_res = [&](int i) { return (res_many && resident_in_group(hs[i])) || res_all; };
@@ -733,11 +741,22 @@ struct SweepParams {
 };
 
 // The launches of n sweeps of h on stream s, sweep indices t, t + 1, ...
-// (plus the device word *tbase when given).
+// (plus the device word *tbase when given), or (tbase null) those of several
+// sweeps in two launches each, in runs of even length, where such are for h.
 hipError_t launch_sweeps(const mcl_lattice* h, const SweepParams& p, int64_t n, uint32_t t, const uint32_t* tbase,
                          hipStream_t s)
 {
-    for (int64_t i = 0; i < n; ++i)
+    int64_t i = 0;
+    const int64_t several = tbase || std::getenv("MCL_SWEEP_GRAPH") ? 0 : mcl::trapezoid_sweeps(h->g);
+    if (several && n > 1)
+        for (int64_t runs = (n + several - 1) / several; runs > 0; --runs) {
+            const int64_t m = (n - i + runs - 1) / runs;
+            const hipError_t e = mcl::launch_trapezoids(h->g, h->model, m, t + (uint32_t)i, h->seed, p.T4, p.T8, p.tb,
+                                                        p.tab, h->lutb, s);
+            if (e != hipSuccess) return e;
+            i += m;
+        }
+    for (; i < n; ++i)
         for (int c = 0; c < 2; ++c) {
             const uint32_t ti = t + (uint32_t)i;
             hipError_t e;
@@ -759,27 +778,21 @@ hipError_t launch_sweeps(const mcl_lattice* h, const SweepParams& p, int64_t n, 
     return hipSuccess;
 }
 
-// Small lattices replay a captured graph of kGraphSweeps sweeps.  Kernels
-// in a graph follow each other sooner than separate launches (a trivial
-// kernel: 2.0 against 2.8 us on the null stream); measured on half-sweeps
-// this saves 0.1-0.4 us each (2-7%) up to L = 2^12 and nothing from 2^13 on,
-// where a half-sweep lasts long enough to hide the dispatch of the next.
-// The environment variable MCL_SWEEP_GRAPH = 0 or 1 turns the replay off or
-// on at any size.
+// The environment variable MCL_SWEEP_GRAPH, read at every call: 0, every
+// half-sweep is a plain launch; 1, calls of kGraphSweeps sweeps or more replay
+// a captured graph of so many (kernels in a graph follow each other 0.1-0.4 us
+// sooner).  Unset, small lattices take fewer launches instead (resident_alone,
+// trapezoid_sweeps) and large ones hide the dispatch of the next launch.
 constexpr int64_t kGraphSweeps = 32;
-constexpr int64_t kGraphMaxCells = int64_t(1) << 24;   // L <= 2^12
 
 bool use_sweep_graph(const mcl_lattice* h)
 {
+    const char* e = std::getenv("MCL_SWEEP_GRAPH");
+    if (!e || e[0] != '1') return false;
     // a stream that the caller is capturing gets plain launches: no graph
     // of the library's own is captured or launched inside the caller's
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
-    if (const char* e = std::getenv("MCL_SWEEP_GRAPH")) {
-        if (e[0] == '0') return false;
-        if (e[0] == '1') return true;
-    }
-    return h->L * h->L <= kGraphMaxCells;
+    return hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
 }
 
 std::mutex g_sweep_capture_mu;
@@ -972,8 +985,9 @@ int group_check(mcl_lattice* const* hs, int count, const int64_t* n, const doubl
 int group_finish(mcl_lattice* const* hs, int count, const int64_t* n, const double* beta, const double* D,
                  bool allow_graph)
 {
+    const bool one = solo(hs, count, n);
     for (int i = 0; i < count; ++i) {
-        if (batched(hs[i], n[i])) {
+        if (batched(hs[i], n[i]) && !one) {
             hs[i]->t += n[i];
         } else if (n[i] > 0) {
             const int rc = sweep_checked(hs[i], n[i], beta[i], D[i], allow_graph);
@@ -1396,7 +1410,7 @@ int group_sweep(mcl_lattice* const* hs, int count, const int64_t* n, const doubl
     std::vector<Span> spans((size_t)std::max(count, 0));
     int rc = group_check(hs, count, n, beta, D, spans.data());
     if (rc || count == 0) return rc;
-    rc = group_run(hs, count, n, beta, D);
+    if (!solo(hs, count, n)) rc = group_run(hs, count, n, beta, D);
     if (rc) return rc;
     return group_finish(hs, count, n, beta, D, true);
 }
@@ -1409,7 +1423,7 @@ int group_sweep_noalloc(mcl_lattice* const* hs, int count, const int64_t* n, con
         std::lock_guard<std::mutex> lk(g_group_mu);
         rc = group_check(hs, count, n, beta, D, g_noalloc_spans);
         if (rc || count == 0) return rc;
-        rc = group_run_noalloc(hs, count, n, beta, D);
+        if (!solo(hs, count, n)) rc = group_run_noalloc(hs, count, n, beta, D);
     }
     if (rc) return rc;
     return group_finish(hs, count, n, beta, D, false);

@@ -79,3 +79,54 @@ def test_batch_of_small_lattices(mcl, noalloc, count, sizes):
         assert lat.t == 2 * n
         assert np.array_equal(lat.read(), want), (model, L, n)
         lat.free()
+
+
+@pytest.mark.parametrize("model,L", [(0, 320), (0, 1088), (0, 1600), (0, 3008), (0, 4096), (0, 4160), (0, 7168), (1, 256),
+                                     (1, 448), (1, 1536), (1, 2112), (1, 5120), (2, 512), (2, 768), (2, 2304),
+                                     (2, 12288)])
+def test_several_sweeps_in_two_launches(mcl, model, L):
+    """The launches that run several sweeps of tiles of rows and then what is
+    left around the cuts: every length of a run of sweeps (2, 3, 4), words and
+    vectors, tile heights that differ by a row, rows that start within a
+    generator block of proposals, the end of the counter."""
+    print("several sweeps", model, L, flush=True)
+    beta, D = _params(model)
+    seed = 5200 + L + model
+    lat = mcl.Lattice(model, L, seed)
+    want = oracle.init(model, L, seed)
+    t = 0
+    for n in (2, 3, 4, 11) if L <= 2304 else (5,):
+        lat.sweep(n, beta, D)
+        oracle.sweep(want, model, seed, t, n, beta, D, nthreads=16)
+        t += n
+        assert lat.t == t
+        assert np.array_equal(lat.read(), want), n
+    if L <= 2304:
+        lat.write(want, 2**32 - 3)
+        lat.sweep(3, beta, D)
+        oracle.sweep(want, model, seed, 2**32 - 3, 3, beta, D, nthreads=16)
+        assert np.array_equal(lat.read(), want)
+    lat.free()
+
+
+@pytest.mark.parametrize("model,L", [(0, 128), (1, 512), (2, 768)])
+def test_caller_captures_several_sweeps(mcl, model, L):
+    """A caller's graph of 7 sweeps, replayed with eager work between."""
+    import torch
+    print("capture", model, L, flush=True)
+    beta, D = _params(model)
+    st = torch.cuda.Stream()
+    lat = mcl.Lattice(model, L, 5300 + model, stream=st)
+    want = lat.read()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        lat.sweep(7, beta, D)
+    for k in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        oracle.sweep(want, model, 5300 + model, 0, 7, beta, D, nthreads=8)
+        assert np.array_equal(lat.read(), want), k
+        x = torch.ones(4096, device="cuda")
+        assert float((x + 1.0).sum()) == 8192.0
+    lat.free()
