@@ -844,14 +844,22 @@ int sweep_checked(mcl_lattice* h, int64_t n, double beta, double D, bool allow_g
 {
     if (n == 0) return MCL_OK;
     SweepParams p{};
-    const bool resident = resident_alone(h, n) && !std::getenv("MCL_SWEEP_GRAPH");
+    const bool few = !std::getenv("MCL_SWEEP_GRAPH");
+    const bool resident = few && resident_alone(h, n);
+    const bool single = few && !resident && n == 1 && mcl::half_by_words(h->g);
     if (h->model == MCL_ISING_LUT) {
         p.tab = lut_device_table(beta);
-        if (!resident) MCL_HIP(mcl::launch_lut_buckets(p.tab, h->lutb, h->stream));
+        if (!resident && !single) MCL_HIP(mcl::launch_lut_buckets(p.tab, h->lutb, h->stream));
     } else if (h->model == MCL_ISING) {
         ising_thresholds(beta, p.T4, p.T8);
     } else {
         bc_table(beta, D, p.tb);
+    }
+    if (single) {
+        for (int c = 0; c < 2; ++c)
+            MCL_HIP(mcl::launch_half_words(h->g, h->model, c, (uint32_t)h->t, h->seed, p.T4, p.T8, p.tb, p.tab, h->stream));
+        h->t += 1;
+        return MCL_OK;
     }
     if (resident) {
         mcl::GroupDesc d = describe(h, n);

@@ -165,6 +165,11 @@ int64_t trapezoid_sweeps(const Geom& g);
 hipError_t launch_trapezoids(const Geom& g, int model, int64_t sweeps, uint32_t t, uint64_t seed,
                              uint32_t T4, uint32_t T8, const BCTable& bc, const LutTable& lt, const void* buckets,
                              hipStream_t s);
+// One half-sweep of a lattice for which half_by_words(), a word per thread
+// (1-bit cells without the bucket table).
+bool half_by_words(const Geom& g);
+hipError_t launch_half_words(const Geom& g, int model, int color, uint32_t t, uint64_t seed, uint32_t T4, uint32_t T8,
+                             const BCTable& bc, const LutTable& lt, hipStream_t s);
 // Bucket tables of the 1-bit replicas of a batched call.
 hipError_t launch_group_lut_buckets(const LutRec* luts, int n, hipStream_t st);
 

@@ -29,6 +29,10 @@ constexpr uint32_t kMaxThreads = 1024;
 // L = 8192 33.6 against 33.9 and 34.7 against 34.0 at three sweeps; 1-bit
 // L = 12288 42.6 against 50.4 (L = 16384 does not fit LDS in 256 tiles).
 constexpr int64_t kTrapezoidMaxL = 7168, kTrapezoidMaxLutL = 12288;
+// The largest whose single sweeps take a word per thread: L = 3072 12.1 against
+// 13.1 us (Blume-Capel 15.4, 16.9), 4096 19.2 against 13.6; 1-bit 4096 13.8
+// against 27.6.
+constexpr int64_t kHalfWordsMaxL = 3072, kHalfWordsMaxLutL = 4096;
 
 // Parameters of the updates of one lattice (tables in LDS).
 struct Rule {
@@ -104,11 +108,19 @@ __device__ __forceinline__ void draw_proposals(uint32_t* bits, uint32_t lo, uint
     }
 }
 
-// props: the proposal blocks of row y.
-template <int MODEL>
+// The word of proposal bits that holds those of in-colour index kv, from the
+// proposal blocks of row y.
+__device__ __forceinline__ uint32_t proposal_word(const uint32_t* props, uint32_t kv, uint32_t y, uint32_t Q)
+{
+    return props[(kv >> 5) - ((y * Q) & ~3u)];
+}
+
+// `proposals(kv)`: the word of proposal bits that holds those of index kv
+// (Blume-Capel).  EXACT: 1-bit cells by the exact table search only.
+template <int MODEL, bool EXACT = false, class P>
 __device__ __forceinline__ void update_word(const Rule& u, char* own, const char* up, const char* row, const char* dn,
                                             uint32_t w, uint32_t W, uint32_t y, uint32_t L, uint32_t c, uint32_t t,
-                                            const uint32_t* props)
+                                            const P& proposals)
 {
     constexpr int CB = MODEL == 2 ? 1 : 4;
     const auto at = [&](const char* r, uint32_t i) { return reinterpret_cast<const uint32_t*>(r)[i]; };
@@ -122,18 +134,23 @@ __device__ __forceinline__ void update_word(const Rule& u, char* own, const char
         const uint32_t d0 = a ^ s, d1 = b ^ s, d2 = mid ^ s, d3 = hs ^ s;
         const uint32_t t1 = d0 ^ d1, u1 = d0 & d1, t2 = d2 ^ d3, u2 = d2 & d3;
         const uint32_t eq4 = ~(d0 | d1 | d2 | d3), eq3 = (t1 ^ t2) & ~(u1 | u2);
-        const uint32_t e4 = dev::lut_word_fast<0>(kv >> 2, t, 8u + 2u * c, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
-        const uint32_t e8 =
-            dev::lut_word_fast<0>(kv >> 2, t, 9u + 2u * c, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax) & e4;
+        const auto draw = [&](uint32_t stream) {
+            if (!EXACT)
+                return dev::lut_word_fast<0>(kv >> 2, t, stream, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
+            const uint32_t blk = kv >> 4;
+            return dev::lut_word(philox4x32_10(blk, 0u, t, stream, u.k0, u.k1),
+                                 philox4x32_10(blk + 1, 0u, t, stream, u.k0, u.k1), u.lut, u.T8, u.kmax);
+        };
+        const uint32_t e4 = draw(8u + 2u * c), e8 = draw(9u + 2u * c) & e4;
         res = ~(s ^ ((eq4 & ~e8) | (eq3 & ~e4)));
     } else {
-        const Philox4 P[2] = {philox4x32_10(kv >> 2, 0u, t, c, u.k0, u.k1),
+        const Philox4 B[2] = {philox4x32_10(kv >> 2, 0u, t, c, u.k0, u.k1),
                               philox4x32_10((kv >> 2) + 1, 0u, t, c, u.k0, u.k1)};
         if (MODEL == 0) {
             uint32_t m4 = 0, m8 = 0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint32_t r = philox_word(P[j >> 2], j & 3), bit = 2u << (4 * j);
+                const uint32_t r = philox_word(B[j >> 2], j & 3), bit = 2u << (4 * j);
                 m4 |= r < u.T4 ? bit : 0u;
                 m8 |= r < u.T8 ? bit : 0u;
             }
@@ -143,7 +160,7 @@ __device__ __forceinline__ void update_word(const Rule& u, char* own, const char
             S = xad(hs, s, S);
             res = s ^ (((S >> 2) | (S & m4) | m8) & 0x22222222u);
         } else {
-            const uint32_t pb = dev::spread8(props[(kv >> 5) - ((y * (W >> 2)) & ~3u)] >> (kv & 31u));
+            const uint32_t pb = dev::spread8(proposals(kv) >> (kv & 31u));
             const uint32_t sum = a + b + mid + hs;
             const uint32_t key = s + s + pb;                            // n * 2 + b, at most 5 per nibble
             const uint32_t ev = ((key & 0x0F0F0F0Fu) << 4) | (sum & 0x0F0F0F0Fu);      // cells 0, 2, 4, 6 as bytes
@@ -155,7 +172,7 @@ __device__ __forceinline__ void update_word(const Rule& u, char* own, const char
 #pragma unroll
             for (int j = 7; j >= 0; --j) {
                 const uint2 e = u.bc[(((j & 1) ? od : ev) >> (8 * (j >> 1))) & 0xFFu];
-                nacc = shl_add<1>(nacc, add_hi(philox_word(P[j >> 2], j & 3), ((uint64_t)e.y << 32) | e.x));
+                nacc = shl_add<1>(nacc, add_hi(philox_word(B[j >> 2], j & 3), ((uint64_t)e.y << 32) | e.x));
             }
             const uint32_t acc = dev::spread8(0u - nacc);
             const uint32_t mask = shl_opaque<4>(acc) - acc;             // 0xF in accepted nibbles
@@ -193,7 +210,7 @@ __device__ __forceinline__ void run_resident(char* lds, uint32_t* extra, uint32_
                 const char* dn = oth + (y + 1 == L ? 0 : y + 1) * rowB;
                 if (WORDS)
                     update_word<MODEL>(rule, own + y * rowB, up, oth + y * rowB, dn, q, U, y, L, c, t,
-                                       extra + (c * L + y) * nb * 4);
+                                       [&](uint32_t kv) { return proposal_word(extra + (c * L + y) * nb * 4, kv, y, Q); });
                 else
                     update_vector<MODEL>(rule, own + y * rowB, up, oth + y * rowB, dn, q, Q, y, L, c, t);
             }
@@ -347,8 +364,9 @@ __global__ __launch_bounds__(kMaxThreads) void trapezoid_kernel(uint32_t* __rest
             const char* oth = lds + ((1 - c) * rows + r) * rowB;
             const uint32_t y = row_of(first, r, L);
             if (WORDS)
-                update_word<MODEL>(rule, own, oth - rowB, oth, oth + rowB, w, W, y, L, c, t + (s >> 1),
-                                   props + (c * rows + r) * nb * 4);
+                update_word<MODEL>(rule, own, oth - rowB, oth, oth + rowB, w, W, y, L, c, t + (s >> 1), [&](uint32_t kv) {
+                    return proposal_word(props + (c * rows + r) * nb * 4, kv, y, Q);
+                });
             else
                 update_vector<MODEL>(rule, own, oth - rowB, oth, oth + rowB, w, Q, y, L, c, t + (s >> 1));
         }
@@ -366,6 +384,41 @@ __global__ __launch_bounds__(kMaxThreads) void trapezoid_kernel(uint32_t* __rest
         if (r >= lo0 && r < hi0) *in_mem(0, r, q) = *in_lds(0, r, q);
         if (r >= lo1 && r < hi1) *in_mem(1, r, q) = *in_lds(1, r, q);
     }
+}
+
+// ---------------------------------------------------------------------------
+// One half-sweep of a small lattice, a thread per word: a thread's chain is a
+// quarter of a vector's and there are four times the waves, without the two
+// row steps of a band.  1-bit cells take the exact search, so that a single
+// sweep needs no bucket table.  One sweep in us, against the band kernels
+// (launching takes about 3.7 of each half): Ising L = 256 7.7 against 8.6, 2048
+// 7.9 against 9.6; Blume-Capel 8.0 against 12.6 and 9.9 against 13.6; 1-bit 9.4
+// against 22.2 and 10.9 against 27.4.
+// ---------------------------------------------------------------------------
+template <int MODEL>
+__global__ __launch_bounds__(256) void half_words_kernel(uint32_t* __restrict__ planes, uint32_t L, uint32_t c, uint32_t t,
+                                                         uint32_t k0, uint32_t k1, uint32_t T4, uint32_t T8, BCTable bc,
+                                                         LutTable lt)
+{
+    constexpr int CB = MODEL == 2 ? 1 : 4;
+    __shared__ ResidentLds tabs;
+    const uint32_t rowB = (L >> 4) * CB, W = rowB >> 2;
+    if (MODEL == 1) dev::load_bc_table(tabs.bc, bc);
+    if (MODEL == 2) {
+        if (threadIdx.x < 16) tabs.lut[threadIdx.x] = lt.T[threadIdx.x];
+        __syncthreads();
+    }
+    const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= L * W) return;
+    const uint32_t y = quotient(g, W, reciprocal(W)), w = g - y * W;
+    char* own = reinterpret_cast<char*>(planes) + (size_t)c * L * rowB + (size_t)y * rowB;
+    const char* oth = reinterpret_cast<const char*>(planes) + (size_t)(1 - c) * L * rowB;
+    const Rule rule{k0, k1, T4, MODEL == 2 ? lt.T[8] : T8, tabs.bc.e, nullptr, tabs.lut, lt.kmax};
+    update_word<MODEL, true>(rule, own, oth + (size_t)(y == 0 ? L - 1 : y - 1) * rowB, oth + (size_t)y * rowB,
+                             oth + (size_t)(y + 1 == L ? 0 : y + 1) * rowB, w, W, y, L, c, t, [&](uint32_t kv) {
+                                 const Philox4 p = philox4x32_10(kv >> 7, 0u, t, 2u + c, k0, k1);
+                                 return philox_word(p, (int)((kv >> 5) & 3));
+                             });
 }
 
 // No more threads than a plane has 16-byte vectors, in whole waves.
@@ -439,6 +492,20 @@ hipError_t launch_trapezoids(const Geom& g, int model, int64_t sweeps, uint32_t 
                      : both(trapezoid_kernel<1, false, false>, trapezoid_kernel<1, false, true>);
     return words ? both(trapezoid_kernel<0, true, false>, trapezoid_kernel<0, true, true>)
                  : both(trapezoid_kernel<0, false, false>, trapezoid_kernel<0, false, true>);
+}
+
+bool half_by_words(const Geom& g) { return g.L <= (g.cb == 1 ? kHalfWordsMaxLutL : kHalfWordsMaxL); }
+
+hipError_t launch_half_words(const Geom& g, int model, int color, uint32_t t, uint64_t seed, uint32_t T4, uint32_t T8,
+                             const BCTable& bc, const LutTable& lt, hipStream_t s)
+{
+    if (!half_by_words(g)) return hipErrorInvalidValue;
+    const uint32_t grid = (uint32_t)((g.plane_words() + 255) / 256);
+    const auto run = [&](auto kernel) {
+        return go(kernel, grid, 256, 0, s, g.plane0, (uint32_t)g.L, (uint32_t)color, t, (uint32_t)seed,
+                  (uint32_t)(seed >> 32), T4, T8, bc, lt);
+    };
+    return model == 0 ? run(half_words_kernel<0>) : model == 1 ? run(half_words_kernel<1>) : run(half_words_kernel<2>);
 }
 
 size_t resident_lds(int model, int64_t L)

@@ -81,12 +81,12 @@ def test_batch_of_small_lattices(mcl, noalloc, count, sizes):
         lat.free()
 
 
-@pytest.mark.parametrize("model,L", [(0, 320), (0, 1088), (0, 1600), (0, 3008), (0, 4096), (0, 4160), (0, 7168), (1, 256),
-                                     (1, 448), (1, 1536), (1, 2112), (1, 5120), (2, 512), (2, 768), (2, 2304),
+@pytest.mark.parametrize("model,L", [(0, 320), (0, 1088), (0, 1600), (0, 3008), (0, 3072), (0, 3136), (0, 4096), (0, 4160), (0, 7168), (1, 256),
+                                     (1, 448), (1, 1536), (1, 2112), (1, 5120), (2, 512), (2, 768), (2, 2304), (2, 4096), (2, 4352),
                                      (2, 12288)])
 def test_several_sweeps_in_two_launches(mcl, model, L):
-    """The launches that run several sweeps of tiles of rows and then what is
-    left around the cuts: every length of a run of sweeps (2, 3, 4), words and
+    """A sweep alone (a word per thread), and the launches that run several
+    sweeps of tiles of rows and then what is left around the cuts: every length of a run of sweeps (2, 3, 4), words and
     vectors, tile heights that differ by a row, rows that start within a
     generator block of proposals, the end of the counter."""
     print("several sweeps", model, L, flush=True)
@@ -95,7 +95,7 @@ def test_several_sweeps_in_two_launches(mcl, model, L):
     lat = mcl.Lattice(model, L, seed)
     want = oracle.init(model, L, seed)
     t = 0
-    for n in (2, 3, 4, 11) if L <= 2304 else (5,):
+    for n in (2, 1, 3, 4, 11) if L <= 2304 else (5, 1):
         lat.sweep(n, beta, D)
         oracle.sweep(want, model, seed, t, n, beta, D, nthreads=16)
         t += n
