@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmcl.so")
-SOURCES = ["api.hip", "sweep.hip", "measure.hip", "pass.hip", "full.hip", "batch.hip", "resident.hip"]  # calibrate.hip is a separate program
+SOURCES = ["api.hip", "sweep.hip", "measure.hip", "pass.hip", "full.hip", "batch.hip", "resident.hip",
+           "io.hip"]  # calibrate.hip is a separate program
 
 # Packed-FP32 instructions are switched off for all device code; the
 # library has no floating point on the device, but the flag keeps the

@@ -197,23 +197,6 @@ int check_params(const mcl_lattice* h, double beta, double D)
     return MCL_OK;
 }
 
-// Cell i of a row (W words) as a spin, for 4-bit cells (n - 1) or 1-bit
-// cells (bit ? +1 : -1).
-int8_t cell_to_spin(const uint32_t* row, int64_t i, int cb)
-{
-    if (cb == 1) return ((row[i >> 5] >> (i & 31)) & 1u) ? (int8_t)1 : (int8_t)-1;
-    return (int8_t)((int)((row[i >> 3] >> (4 * (i & 7))) & 0xFu) - 1);
-}
-
-void spin_to_cell(uint32_t* row, int64_t i, int s, int cb)
-{
-    if (cb == 1) {
-        if (s > 0) row[i >> 5] |= 1u << (i & 31);
-        return;
-    }
-    row[i >> 3] |= (uint32_t)(s + 1) << (4 * (i & 7));
-}
-
 // ---------------------------------------------------------------------------
 // Batched path.
 // ---------------------------------------------------------------------------
@@ -957,6 +940,50 @@ private:
     PinnedBuffer b_;
 };
 
+// Rows of spins through two pinned buffers in turn, kChunkBytes of rows at a
+// time: `queue` puts the kernel for rows [row, row + n) and a buffer on the
+// stream, `host` reads or writes the buffer's host side -- after the kernel
+// when the spins come from the device, before it when they go there.
+constexpr int64_t kChunkBytes = int64_t(4) << 20;
+struct Event {
+    hipEvent_t e = nullptr;
+    ~Event()
+    {
+        if (e) (void)hipEventDestroy(e);
+    }
+};
+template <class Q, class H>
+int stream_rows(hipStream_t stream, int64_t rows, int64_t row_bytes, bool to_host, Q queue, H host)
+{
+    const int64_t step = std::max<int64_t>(1, std::min(rows, kChunkBytes / row_bytes));
+    const int64_t chunks = (rows + step - 1) / step;
+    Event done[2];
+    Pinned buf[2] = {Pinned(stream), Pinned(stream)};
+    for (int k = 0; k < (int)std::min<int64_t>(2, chunks); ++k) {
+        MCL_HIP(buf[k].take((size_t)(step * row_bytes)));
+        MCL_HIP(hipEventCreateWithFlags(&done[k].e, hipEventDisableTiming));
+    }
+    const auto size = [&](int64_t c) { return std::min(step, rows - c * step); };
+    for (int64_t c = 0; c < chunks + (to_host ? 1 : 0); ++c) {
+        // chunk c on its way; when reading, chunk c - 1 taken meanwhile
+        if (c < chunks) {
+            Pinned& b = buf[c & 1];
+            if (!to_host) {
+                if (c >= 2) MCL_HIP(hipEventSynchronize(done[c & 1].e));       // its last kernel has read it
+                host(c * step, size(c), b.host());
+            }
+            MCL_HIP(queue(c * step, size(c), b.device()));
+            MCL_HIP(hipEventRecord(done[c & 1].e, stream));
+        }
+        if (to_host && c >= 1) {
+            MCL_HIP(hipEventSynchronize(done[(c - 1) & 1].e));
+            host((c - 1) * step, size(c - 1), buf[(c - 1) & 1].host());
+        }
+    }
+    if (!to_host) MCL_HIP(hipStreamSynchronize(stream));
+    return MCL_OK;
+}
+
 // ---------------------------------------------------------------------------
 // Argument checks and the lattices outside the batched launches, shared by
 // group_sweep and group_sweep_noalloc.
@@ -1362,55 +1389,46 @@ int lattice_write_packed(mcl_lattice* h, const void* host, int64_t bytes, int64_
 int lattice_read(mcl_lattice* h, int8_t* host_spins)
 {
     if (!h || !host_spins) return MCL_EARG;
-    const int64_t L = h->L, W = h->g.W;
-    std::vector<uint32_t> buf((size_t)(2 * L * W));
-    const int rc = lattice_read_packed(h, buf.data(), (int64_t)buf.size() * 4);
-    if (rc) return rc;
-    for (int64_t y = 0; y < L; ++y)
-        for (int64_t x = 0; x < L; ++x) {
-            const int c = (int)((x + y) & 1);
-            host_spins[y * L + x] = cell_to_spin(buf.data() + (size_t)(c * L * W + y * W), x >> 1, h->g.cb);
-        }
-    return MCL_OK;
+    const int64_t L = h->L;
+    return stream_rows(
+        h->stream, L, L, true,
+        [&](int64_t row, int64_t n, void* dev) { return mcl::launch_unpack(h->g, row, n, dev, h->stream); },
+        [&](int64_t row, int64_t n, const void* host) { std::memcpy(host_spins + row * L, host, (size_t)(n * L)); });
 }
 
 int lattice_read_window(mcl_lattice* h, int64_t x0, int64_t y0, int64_t w, int64_t hgt, int8_t* host_spins)
 {
     if (!h || !host_spins) return MCL_EARG;
-    const int64_t L = h->L, W = h->g.W;
+    const int64_t L = h->L;
     if (w <= 0 || hgt <= 0 || w > L || hgt > L || x0 < 0 || y0 < 0 || x0 >= L || y0 >= L) return MCL_ERANGE;
-    MCL_HIP(hipStreamSynchronize(h->stream));
-    std::vector<uint32_t> rows((size_t)(2 * W));
-    for (int64_t dy = 0; dy < hgt; ++dy) {
-        const int64_t y = (y0 + dy) % L;
-        for (int c = 0; c < 2; ++c)
-            MCL_HIP(hipMemcpyAsync(rows.data() + c * W, h->g.plane(c) + y * W, W * 4, hipMemcpyDeviceToHost,
-                                   h->stream));
-        MCL_HIP(hipStreamSynchronize(h->stream));
-        for (int64_t dx = 0; dx < w; ++dx) {
-            const int64_t x = (x0 + dx) % L;
-            const int c = (int)((x + y) & 1);
-            host_spins[dy * w + dx] = cell_to_spin(rows.data() + (size_t)(c * W), x >> 1, h->g.cb);
-        }
-    }
-    return MCL_OK;
+    return stream_rows(
+        h->stream, hgt, w, true,
+        [&](int64_t row, int64_t n, void* dev) { return mcl::launch_window(h->g, x0, y0 + row, w, n, dev, h->stream); },
+        [&](int64_t row, int64_t n, const void* host) { std::memcpy(host_spins + row * w, host, (size_t)(n * w)); });
 }
 
 int lattice_write(mcl_lattice* h, const int8_t* host_spins, int64_t t)
 {
     if (!h || !host_spins) return MCL_EARG;
     if (t < 0 || t > (int64_t(1) << 32)) return MCL_ERANGE;
-    const int64_t L = h->L, W = h->g.W;
-    std::vector<uint32_t> buf((size_t)(2 * L * W), 0u);
-    for (int64_t y = 0; y < L; ++y)
-        for (int64_t x = 0; x < L; ++x) {
-            const int s = host_spins[y * L + x];
-            const bool ok = (h->model != MCL_BC) ? (s == 1 || s == -1) : (s >= -1 && s <= 1);
-            if (!ok) return MCL_ESPINS;
-            const int c = (int)((x + y) & 1);
-            spin_to_cell(buf.data() + (size_t)(c * L * W + y * W), x >> 1, s, h->g.cb);
-        }
-    return lattice_write_packed(h, buf.data(), (int64_t)buf.size() * 4, t);
+    const int64_t L = h->L;
+    // every spin is checked before the first is written
+    for (int64_t y = 0; y < L; ++y) {
+        const int8_t* row = host_spins + y * L;
+        unsigned bad = 0;
+        if (h->model == MCL_BC)
+            for (int64_t x = 0; x < L; ++x) bad |= (unsigned)(row[x] + 1) > 2u;
+        else
+            for (int64_t x = 0; x < L; ++x) bad |= (unsigned)(row[x] + 1) & ~2u;
+        if (bad) return MCL_ESPINS;
+    }
+    const int rc = stream_rows(
+        h->stream, L, L, false,
+        [&](int64_t row, int64_t n, const void* dev) { return mcl::launch_pack(h->g, row, n, dev, h->stream); },
+        [&](int64_t row, int64_t n, void* host) { std::memcpy(host, host_spins + row * L, (size_t)(n * L)); });
+    if (rc) return rc;
+    h->t = t;
+    return MCL_OK;
 }
 
 int group_sweep(mcl_lattice* const* hs, int count, const int64_t* n, const double* beta, const double* D)

@@ -44,6 +44,13 @@ hipError_t launch_bc_half(const Geom& g, const HalfSweepArgs& a, hipStream_t s);
 // it can sit in a captured graph).
 hipError_t launch_set_word(uint32_t* p, uint32_t v, bool add, hipStream_t s);
 
+// Rows [y0, y0 + rows) to int8 spins in pinned host memory and back, and rows
+// y0 .. (periodic, y0 < 2 L) of the window of columns [x0, x0 + w); at most
+// 2^31 spins.
+hipError_t launch_unpack(const Geom& g, int64_t y0, int64_t rows, void* out, hipStream_t s);
+hipError_t launch_pack(const Geom& g, int64_t y0, int64_t rows, const void* in, hipStream_t s);
+hipError_t launch_window(const Geom& g, int64_t x0, int64_t y0, int64_t w, int64_t rows, void* out, hipStream_t s);
+
 // Measurement kernels accumulating into int64 device scratch.
 // acc layout: [0] B, [1] M (from +1 count minus -1 count), [2] #(+1),
 // [3] #(-1), [4] #(0), [5..13] the sigma-h histogram, [14], [15] below; cells
