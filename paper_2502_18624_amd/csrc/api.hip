@@ -336,18 +336,17 @@ bool resident_in_group(const mcl_lattice* h)
 // Sweeps of one resident launch (about 2 ms at L = 256).
 constexpr int64_t kResidentSweeps = 256;
 
-// Band height of a replica: the tuning's for its size, halved `shift` times
-// and as often as it takes to fill a tile of 256 threads, but at least 2 rows.
-// A call whose replicas give few threads needs the shorter bands as a single
-// small lattice does (band_rows in sweep.hip): until there are kGroupThreads,
-// four rounds of workgroups at the four waves per SIMD of the mixed kernels,
-// a launch waits for its last, partly filled round.  48 replicas of L = 512 ..
-// 8192, 4 sweeps: 2.28 ms, against 2.41 at 2^19 threads, 2.85 with the tuning's
-// bands and 2.24 at 2^22, whose short bands read more halo rows.
+// Band height of a replica: the tuning's for its size, but at most `cap` rows
+// and few enough to fill a tile of 256 threads (at least 2).  A call whose
+// replicas give few threads needs the shorter bands as a single small lattice
+// does (band_rows in sweep.hip): the cap goes down from 64 until there are
+// kGroupThreads, since a launch of a few rounds of workgroups waits for its
+// last, partly filled one.  48 replicas of L = 512 .. 8192, 4 sweeps:
+// 2.02 ms, with 2^19 threads 2.29, 2^21 2.09, the tuning's bands 2.80.
 constexpr int64_t kGroupThreads = int64_t(1) << 20;
-int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int shift)
+int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int64_t cap)
 {
-    int64_t rows = std::max<int64_t>(2, tun.rows_log2L[log2_floor(h->L)] >> shift);
+    int64_t rows = std::min<int64_t>(cap, tun.rows_log2L[log2_floor(h->L)]);
     while (rows > 2 && h->g.Q * (h->L / rows) < 256) rows >>= 1;
     return rows;
 }
@@ -386,18 +385,21 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         }
     const bool res_many = fit >= kResidentMany, res_all = small == all;
     const auto is_res = [&](int i) { return (res_many && resident_in_group(hs[i])) || res_all; };
-    int64_t threads_all = 0;
     for (int i = 0; i < count; ++i)
         if (batched(hs[i], n[i])) {
             const bool res = is_res(i);
             (res ? img.res_nmax : img.nmax) = std::max(res ? img.res_nmax : img.nmax, n[i]);
-            if (!res) threads_all += hs[i]->g.Q * (hs[i]->L / tun.rows_log2L[log2_floor(hs[i]->L)]);
             img.ndesc++;
             img.nbc += hs[i]->model == MCL_BC;
             img.nlut += hs[i]->model == MCL_ISING_LUT;
         }
-    int shift = 0;
-    while (shift < 5 && (threads_all << shift) < kGroupThreads) ++shift;
+    int64_t cap = 128;
+    for (int64_t threads = 0; cap > 2 && threads < kGroupThreads;) {
+        cap >>= 1;
+        threads = 0;
+        for (int i = 0; i < count; ++i)
+            if (batched(hs[i], n[i]) && !is_res(i)) threads += hs[i]->g.Q * (hs[i]->L / group_rows(hs[i], tun, cap));
+    }
     img.off_bc = align_up(img.ndesc * sizeof(mcl::GroupDesc), 256);
     img.off_lut = align_up(img.off_bc + img.nbc * 96 * sizeof(uint2), 256);
     img.off_s = align_up(img.off_lut + img.nlut * sizeof(mcl::LutRec), 256);
@@ -435,7 +437,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         for (int j = 0; j < cnt; ++j) {
             const int i = order[j];
             const mcl_lattice* h = hs[i];
-            const uint32_t rows = (uint32_t)group_rows(h, tun, shift);
+            const uint32_t rows = (uint32_t)group_rows(h, tun, cap);
             const int64_t threads = h->g.Q * (h->L / rows);
             ln.mask |= h->model == MCL_ISING ? mcl::kMaskIsing : h->model == MCL_BC ? mcl::kMaskBC : mcl::kMaskLut;
             if (res) {
