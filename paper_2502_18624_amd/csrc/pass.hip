@@ -59,13 +59,14 @@ template <int MODEL>
 struct Shape {
     static constexpr int CB = MODEL == 2 ? 1 : 4;
     static constexpr int NB = MODEL == 1 ? 2 : 1;           // bit planes of a cell
-    static constexpr int NC = MODEL == 2 ? 4 : 2;           // 32-cell vectors per lane, row block and U_p
+    static constexpr int NC = MODEL == 2 ? 4 : MODEL == 1 ? 1 : 2;  // 32-cell vectors per lane, row block and U_p
     static constexpr int NV = 4 * NC;                       // vectors of a strip row
     static constexpr int RAW = MODEL == 2 ? 1 : NC;         // 16-byte loads for them
     static constexpr int WAVES = MODEL == 2 ? 2 : 4;        // a workgroup's strips, side by side
     static constexpr int ROWB = WAVES * NV * 16 + 16;       // LDS bytes of its row (16 for halo cells)
     static constexpr int CELLB = 2 * kTileRows * ROWB + 16;
-    static constexpr int TW = NV / 8;                       // T words of a strip row
+    static constexpr bool HALF = NV == 4;                   // a strip row gives half a T word
+    static constexpr int TW = HALF ? 1 : NV / 8;            // (half) T words of a strip row
     static constexpr int TB = NB * TW * 16 * 16 * 4;        // T words of 16 row blocks
     static constexpr int RB = MODEL == 0 ? 16 * 16 * 4 : 0; // packed words of 16 sampled rows
     // vector of lane group h at index c
@@ -454,13 +455,17 @@ __global__ __launch_bounds__(64 * Shape<MODEL>::WAVES) __attribute__((amdgpu_wav
                 const uint32_t NSW = L >> 9;
 #pragma unroll 1
                 for (int k = 0; k < NB * S::TW; ++k) {
-                    const uint32_t word = strip * S::TW + (k % S::TW);
+                    const uint32_t word = S::HALF ? strip >> 1 : strip * S::TW + (k % S::TW);
                     if (word >= NSW) continue;
                     uint32_t* out = tb + (size_t)(k / S::TW) * L * NSW + (size_t)word * L;
 #pragma unroll 1
                     for (uint32_t i = lane; i < 256; i += 64) {
                         const uint32_t rho = i >> 4, s = i & 15;
-                        if (s >= from && s <= to) out[rho * NS + b0 + s] = tbuf[k * 256 + i];
+                        if (s < from || s > to) continue;
+                        if (S::HALF)
+                            reinterpret_cast<uint16_t*>(out + rho * NS + b0 + s)[strip & 1u] = (uint16_t)tbuf[k * 256 + i];
+                        else
+                            out[rho * NS + b0 + s] = tbuf[k * 256 + i];
                     }
                 }
                 if (MODEL == 0 && strip < NSW) {
@@ -555,7 +560,7 @@ hipError_t launch_pass(const Geom& g, int model, int64_t* Cx, int64_t* Cy, int64
 {
     if ((rbits != nullptr) != (tbits != nullptr && model == 0)) return hipErrorInvalidValue;
     if (tbits && (g.L < 512 || (g.L & (g.L - 1)) != 0)) return hipErrorInvalidValue;
-    const int64_t per = model == 2 ? 4 : 8;                       // 16-byte units of a strip row
+    const int64_t per = model == 0 ? 8 : 4;                       // 16-byte units of a strip row
     const uint32_t waves = model == 2 ? 2 : 4;
     const uint32_t nstrips = (uint32_t)((g.Q + per * waves - 1) / (per * waves));
     const int64_t RT = g.L / kTileRows;
