@@ -53,7 +53,7 @@ __device__ __forceinline__ void wave_order()
 constexpr int kTileRows = 32;               // rows of a tile: two blocks of 16
 // Tiles of a unit (a wave's run down its strip): an accumulator takes at most
 // 16 products of at most 128 per tile, far below 2^22.
-constexpr int kMaxTiles = 2048;
+constexpr int kMaxTiles = 64;
 
 template <int MODEL>
 struct Shape {
