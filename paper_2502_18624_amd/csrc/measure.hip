@@ -468,9 +468,12 @@ __global__ __launch_bounds__(256) void tbits_kernel(const uint32_t* __restrict__
 // source words as broadcast 16-byte loads, and keeps its sum in a register
 // over all the workgroup's rows; one atomic per distance and workgroup at
 // the end.  Workgroups of 512 threads, several per CU, so one loads its next
-// row while another works on its own.  For 4-bit Ising lattices measured with
-// the fused short-distance tiles (rb set) the residue rows come ready from
-// those tiles, and the row's 4-bit cells are not read at all.
+// row while another works on its own.  For 4-bit Ising lattices from L = 512
+// on (rb set) the residue rows come ready from the measurement pass, and the
+// row's 4-bit cells are not read at all.  (Lanes over the words and a wave's
+// distances in registers, which frees the LDS reads of bank conflicts, took
+// 193 us at L = 2^17 where this takes 162: a third of the time is building
+// the rows, and 64 sums to reduce per wave cost what the conflicts did.)
 //
 // Building the residue rows (L >= 512): a 4-bit word w of plane c holds the
 // cells x = 16 w + 2 j + c, j = 0 .. 7, i.e. bit w of residues 2 j + c, so a
@@ -727,8 +730,9 @@ __global__ __launch_bounds__(kSxThreads) void corr_sxb_kernel(const uint32_t* __
 // neighbouring lanes reading neighbouring words.  Each word of the T bits is
 // read once as a partner, however many distances there are, and the kernel is
 // bound by the LDS reads.  4-bit Ising L = 2^17, 480 distances: 0.23 ms; with
-// the T bits row by row, partners read from the last-level cache, 0.43.  STAGED false: classes that do not fit LDS are read
-// from memory (L = 2^20, and Blume-Capel at L = 2^19).
+// the T bits row by row, partners read from the last-level cache, 0.43.
+// STAGED false: classes that do not fit LDS are read from memory (L = 2^20,
+// and Blume-Capel at L = 2^19).
 // DIFF (Ising from L = 512 on): no word has invalid bits, so the sum is 32 per
 // word minus twice the count of differing bits, which is all the loop counts.
 constexpr int kYGroup = 8;

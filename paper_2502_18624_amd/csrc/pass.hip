@@ -21,18 +21,19 @@
 // of target rows cover r = 0 .. 32.  Along x the operands are 16 columns by
 // 128 rows, read from LDS by the transposing ds_read_b64_tr_b4: seven
 // products per block of 16 columns.  One wave walks down a strip of columns
-// (256 four-bit or 512 one-bit cells of a plane row) in tiles of 32 rows, its
+// (256 four-bit, 128 Blume-Capel or 512 one-bit cells of a plane row) in tiles of 32 rows, its
 // fragments of the tile before in registers, so every cell is read from
 // memory once and staged in LDS once.  The waves of a workgroup take strips
 // side by side and read their neighbours' edge cells from LDS.
 //
 // What it replaced counted xors of bit words, 2 to 3 VALU instructions per
 // 32 pairs of 64 distances, and was bound by VALU issue.  Measured, before and
-// after, the B/M/Q work included: 4-bit Ising L = 2^17 4.00 -> 2.18 ms (8.6 GB:
-// 3.9 TB/s, bound by memory reads: a kernel that only loads in this pattern
-// takes 1.42), 1-bit L = 2^16 0.85 -> 0.31 ms (matrix and VALU issue),
-// Blume-Capel L = 2^15 0.87 -> 0.41 ms.  Edge cells read from memory by each
-// wave, not each workgroup, made it 2.9 ms at L = 2^17.
+// after, the B/M/Q work included: 4-bit Ising L = 2^17 4.00 -> 1.96 ms (8.6 GB:
+// 4.4 TB/s, bound by memory reads: a kernel that only loads in this pattern
+// takes 1.42), 1-bit L = 2^16 0.85 -> 0.30 ms (matrix and VALU issue),
+// Blume-Capel L = 2^15 0.87 -> 0.17 ms (0.54 GB: 3.1 TB/s; VALU issue beside
+// the reads).  Edge cells read from memory by each wave, not each workgroup,
+// made it 2.9 ms at L = 2^17.
 #include <algorithm>
 #include <type_traits>
 
@@ -51,10 +52,17 @@ __device__ __forceinline__ void wave_order()
 }
 
 constexpr int kTileRows = 32;               // rows of a tile: two blocks of 16
-// Tiles of a unit (a wave's run down its strip): an accumulator takes at most
-// 16 products of at most 128 per tile, far below 2^22.
+// Tiles of a unit (a wave's run down its strip).  An accumulator takes at most
+// 16 products of at most 128 per tile: below 2^22 for 2048 tiles.  Runs of 64,
+// several rounds of workgroups at L = 2^17, end more evenly than one round of
+// 512 tiles each: one measurement 2.36 against 2.57 ms (runs of 32 2.33, but
+// Blume-Capel L = 2^15 and 1-bit L = 2^16, one round with runs of 64, 2% slower).
 constexpr int kMaxTiles = 64;
 
+// Strips: 256 four-bit cells (with 128, half a row of fragments per lane, the
+// measurement at L = 2^17 takes 2.50 against 2.36 ms), but 128 for
+// Blume-Capel, whose two bit planes of 256 need 148 registers more than there
+// are (0.41 against 0.17 ms at L = 2^15).
 template <int MODEL>
 struct Shape {
     static constexpr int CB = MODEL == 2 ? 1 : 4;
