@@ -283,6 +283,10 @@ struct GroupLaunch {
     uint32_t total;    // tiles
     uint32_t grid;     // workgroups (a multiple of 8)
 };
+// The block at off_s: the sweep-offset word, 16 claim counters from word 16 on,
+// and 9 words for each launch from word 32 on: where the XCDs' shares of its
+// tiles begin and end.
+constexpr size_t kShareWord = 32;
 struct GroupImage {
     GroupLaunch launches[3];   // batched: one per model, or one for all
     int nlaunch = 0;
@@ -350,6 +354,12 @@ int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int64_t ca
     while (rows > 2 && h->g.Q * (h->L / rows) < 256) rows >>= 1;
     return rows;
 }
+
+// Cost of a 16-byte vector by model: the VALU instructions of its updates (32
+// of 14.8 and 18 for 4-bit cells, 128 of 7.55 for 1-bit cells).  The XCDs take
+// their shares of a launch's tiles by it.  54 mixed replicas of L = 256 .. 5202,
+// 4 sweeps: 937 us, with eighths of the tiles (one XCD 10% above the mean) 984.
+constexpr uint32_t kVectorCost[3] = {15, 18, 31};
 
 // Descriptor of h for n sweeps, without its launch's fields and its tables.
 mcl::GroupDesc describe(const mcl_lattice* h, int64_t n)
@@ -433,7 +443,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
             std::sort(order, order + cnt,
                       [&](int a, int b) { return hs[a]->L != hs[b]->L ? hs[a]->L > hs[b]->L : a < b; });
         GroupLaunch ln{0, k, cnt, 0, 0};
-        uint64_t tiles = 0;
+        uint64_t tiles = 0, cost = 0;
         for (int j = 0; j < cnt; ++j) {
             const int i = order[j];
             const mcl_lattice* h = hs[i];
@@ -470,6 +480,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
             nl += h->model == MCL_ISING_LUT;
             ++k;
             tiles += (uint64_t)((threads + 255) / 256);
+            cost += (uint64_t)((threads + 255) / 256) * rows * kVectorCost[h->model];
         }
         if (res) {
             img.nres = cnt;
@@ -477,9 +488,28 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         }
         if (tiles >= (uint64_t(1) << 32)) return MCL_ERANGE;
         ln.total = (uint32_t)tiles;
-        // one workgroup per tile, or a persistent grid of wg_per_cu per CU;
-        // a multiple of 8 either way (one share per XCD)
-        uint64_t grid = (tiles + 7) / 8 * 8;
+        // each XCD's share of the tiles, an eighth of their cost
+        uint64_t share[9] = {0}, sum = 0, most = 0;
+        int part = 1;
+        tiles = 0;
+        for (int j = 0; j < cnt; ++j) {
+            const mcl_lattice* h = hs[order[j]];
+            const int64_t rows = group_rows(h, tun, cap);
+            const uint64_t one = (uint64_t)rows * kVectorCost[h->model];
+            const uint64_t k = (uint64_t)((h->g.Q * (h->L / rows) + 255) / 256);
+            for (; part < 8 && cost * part / 8 <= sum + k * one; ++part) share[part] = tiles + (cost * part / 8 - sum) / one;
+            sum += k * one;
+            tiles += k;
+        }
+        share[8] = tiles;
+        for (int p = 0; p < 8; ++p) most = std::max(most, share[p + 1] - share[p]);
+        if (base)
+            for (int p = 0; p < 9; ++p)
+                ((uint32_t*)(base + img.off_s))[kShareWord + 9 * img.nlaunch + p] = (uint32_t)share[p];
+        // one workgroup per tile of the longest share, or a persistent grid of
+        // wg_per_cu per CU; a multiple of 8 either way (one share per XCD)
+        uint64_t grid = 8 * most;
+        if (grid > (uint64_t(1) << 24)) grid = (tiles + 7) / 8 * 8;    // (some then take two)
         if (tun.wg_per_cu > 0) grid = std::min<uint64_t>(grid, (uint64_t)cus * tun.wg_per_cu / 8 * 8);
         grid = std::max<uint64_t>(grid, 8);
         if (grid > (uint64_t(1) << 24)) return MCL_ERANGE;
@@ -498,13 +528,14 @@ hipError_t group_launches(const GroupImage& img, const void* dev, int64_t s0, in
     const mcl::GroupDesc* desc = (const mcl::GroupDesc*)b;
     const uint2* tabs = (const uint2*)(b + img.off_bc);
     const mcl::LutRec* luts = (const mcl::LutRec*)(b + img.off_lut);
-    uint32_t* ctr = (uint32_t*)(b + img.off_s) + 16;
+    uint32_t* words = (uint32_t*)(b + img.off_s);
     for (int64_t s = s0; s < s0 + k; ++s)
         for (int c = 0; c < 2; ++c)
             for (int j = 0; j < img.nlaunch; ++j) {
                 const GroupLaunch& ln = img.launches[j];
                 const hipError_t e = mcl::launch_group_half(ln.mask, c, desc + ln.first, ln.count, ln.total, ln.grid,
-                                                            tabs, luts, (uint32_t)s, sbase, ctr, st);
+                                                            words + kShareWord + 9 * j, tabs, luts, (uint32_t)s, sbase,
+                                                            words + 16, st);
                 if (e != hipSuccess) return e;
             }
     return hipSuccess;

@@ -150,13 +150,13 @@ constexpr int kMaskIsing = 1, kMaskBC = 2, kMaskLut = 4;
 
 // One colour of sweep s (+ *sbase when sbase is set) for every replica of
 // the list with s < n; grid workgroups (a multiple of 8) walk the `total`
-// tiles, each XCD's workgroups one contiguous eighth of the list.  With
-// fewer workgroups than tiles they claim tiles from the 16 counter words at
-// ctr, which must be zero before the first such launch and are zero again
-// after each (nullptr: a fixed share per workgroup).
+// tiles, those of XCD x the tiles share[x] .. share[x + 1] - 1.  With fewer
+// workgroups than tiles they claim tiles from the 16 counter words at ctr,
+// which must be zero before the first such launch and are zero again after
+// each (nullptr: a fixed walk).
 hipError_t launch_group_half(int mask, int color, const GroupDesc* desc, int count, uint32_t total,
-                             uint32_t grid, const uint2* bc_tables, const LutRec* luts, uint32_t s,
-                             const uint32_t* sbase, uint32_t* ctr, hipStream_t st);
+                             uint32_t grid, const uint32_t* share, const uint2* bc_tables, const LutRec* luts,
+                             uint32_t s, const uint32_t* sbase, uint32_t* ctr, hipStream_t st);
 // Lattices that a workgroup holds in LDS (resident_lds bytes of it: both
 // planes, and the bucket table of 1-bit cells), in one launch: n sweeps of a
 // single lattice with its tables by value, or sweeps [s0, min(s1, n)) of

@@ -130,3 +130,33 @@ def test_caller_captures_several_sweeps(mcl, model, L):
         x = torch.ones(4096, device="cuda")
         assert float((x + 1.0).sum()) == 8192.0
     lat.free()
+
+
+@pytest.mark.parametrize("wg_per_cu,split", [(0, 0), (2, 0), (0, 1)])
+@pytest.mark.parametrize("reps", [
+    [(2, 2048)] + [(0, 320)] * 9,                                # most of the cost at the front,
+    [(0, 320)] * 9 + [(1, 1088), (2, 1536)],                     # at the back
+    [(2, 768), (0, 64)],                                         # fewer tiles than XCDs
+    [(0, 640), (1, 704), (2, 1024), (0, 1472), (1, 64), (2, 256), (0, 1024)],
+])
+def test_shares_of_a_mixed_batch(mcl, reps, wg_per_cu, split):
+    """The XCDs' shares of a batched launch, divided by cost: replicas of very
+    different cost, shares that begin inside a replica or are empty, one
+    workgroup per tile and fewer; a call three times, the last a replay."""
+    from paper_2502_18624_amd import autotune
+    print("shares", reps, wg_per_cu, split, flush=True)
+    old, tuning = autotune.get_tuning(), autotune.get_tuning()
+    tuning.wg_per_cu, tuning.split_models, tuning.use_graph = wg_per_cu, split, 1
+    n = [3 - i % 2 for i in range(len(reps))]
+    lats = [mcl.Lattice(m, L, 5400 + i) for i, (m, L) in enumerate(reps)]
+    autotune.set_tuning(tuning)
+    try:
+        for _ in range(3):
+            mcl.group_sweep(lats, n, [_params(m)[0] for m, _ in reps], [_params(m)[1] for m, _ in reps])
+    finally:
+        autotune.set_tuning(old)
+    for i, (lat, (model, L)) in enumerate(zip(lats, reps)):
+        want = oracle.init(model, L, 5400 + i)
+        oracle.sweep(want, model, 5400 + i, 0, 3 * n[i], *_params(model), nthreads=16)
+        assert np.array_equal(lat.read(), want), (i, model, L)
+        lat.free()
