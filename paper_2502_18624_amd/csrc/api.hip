@@ -346,10 +346,13 @@ constexpr int64_t kResidentSweeps = 256;
 // does (band_rows in sweep.hip): the cap goes down from 64 until there are
 // kGroupThreads, since a launch of a few rounds of workgroups waits for its
 // last, partly filled one.  48 replicas of L = 512 .. 8192, 4 sweeps:
-// 2.02 ms, with 2^19 threads 2.29, 2^21 2.09, the tuning's bands 2.80.
+// 2.02 ms, with 2^19 threads 2.29, 2^21 2.09, the tuning's bands 2.80.  1-bit
+// replicas take half the cap, as a row costs them twice as much and the last
+// tiles are waited for: 1.90 ms.
 constexpr int64_t kGroupThreads = int64_t(1) << 20;
 int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int64_t cap)
 {
+    if (h->model == MCL_ISING_LUT) cap = std::max<int64_t>(2, cap / 2);
     int64_t rows = std::min<int64_t>(cap, tun.rows_log2L[log2_floor(h->L)]);
     while (rows > 2 && h->g.Q * (h->L / rows) < 256) rows >>= 1;
     return rows;
