@@ -8,22 +8,35 @@
 namespace mcl {
 namespace {
 
-
 // ---------------------------------------------------------------------------
 // Initial state.  One thread per word index (row y, word wd) of both planes
 // (8 four-bit or 32 one-bit cells each): they hold the 16 (64) consecutive
 // sites from x = 16 wd (64 wd) on, so each generator block of 4 sites is
 // computed once and gives two cells of each plane -- even x those of plane
 // y & 1, odd x those of the other.  Bound by the generator's VALU work,
-// L^2 / 4 blocks.  With a block per cell it took 5.44 ms of a 1-bit quench at
-// L = 2^16 (4 sweeps, 3 measurements: 11.9 ms in all, 8.2 with this one).
+// L^2 / 4 blocks: 1.24 ms for 1-bit cells at L = 2^16, where 40 lane
+// instructions a block take 1.09 (with a block per cell 5.44, with a compare
+// and a shift per cell 1.40); Blume-Capel 1.62 (1.94), Ising L = 2^17 5.8 (6.1).
 // ---------------------------------------------------------------------------
-// The cell of initial draw w: n = s + 1 (4-bit cells) or the bit [s > 0].
+// Cells come in from the highest to the lowest, so that each takes one funnel
+// shift of its draw w: a 1-bit cell is w's top bit negated (+1 iff w < 2^31)
+// and a 4-bit Ising cell twice that, both negated (and the other bits of w
+// cleared) for the whole word at the end; a Blume-Capel cell is floor(3 w / 2^32).
 template <int MODEL>
-__device__ __forceinline__ uint32_t init_cell(uint32_t w)
+__device__ __forceinline__ uint32_t init_next(uint32_t cells, uint32_t w)
 {
-    if (MODEL == 1) return (w >= 0x55555556u ? 1u : 0u) + (w >= 0xAAAAAAABu ? 1u : 0u);   // floor(3 w / 2^32)
-    return MODEL == 0 ? (~w >> 31) << 1 : ~w >> 31;                                       // +1 iff w < 2^31
+    if (MODEL == 1) {
+        uint64_t w3;                                            // (v_mul_hi_u32 issues at a quarter of the rate)
+        asm("v_mad_u64_u32 %0, vcc, %1, 3, 0" : "=v"(w3) : "v"(w) : "vcc");
+        return shl_or<4>(cells, (uint32_t)(w3 >> 32));
+    }
+    return funnel(cells, w, MODEL == 0 ? 28 : 31);
+}
+
+template <int MODEL>
+__device__ __forceinline__ uint32_t init_word(uint32_t cells)
+{
+    return MODEL == 0 ? (~cells & 0x88888888u) >> 2 : MODEL == 1 ? cells : ~cells;
 }
 
 template <int MODEL>
@@ -39,12 +52,14 @@ __global__ __launch_bounds__(256) void init_kernel(uint32_t* __restrict__ planes
         const uint64_t blk = g * BLOCKS;        // (y L + x) / 4, x = 2 CELLS wd and L = 2 CELLS W
         uint32_t even = 0, odd = 0;
 #pragma unroll
-        for (int b = 0; b < BLOCKS; ++b) {
+        for (int b = BLOCKS - 1; b >= 0; --b) {
             const uint64_t n = blk + b;
             const Philox4 o = philox4x32_10(dev::lo32(n), dev::hi32(n), 0u, 4u, k0, k1);
-            even |= init_cell<MODEL>(o.v0) << (2 * CB * b) | init_cell<MODEL>(o.v2) << (2 * CB * b + CB);
-            odd |= init_cell<MODEL>(o.v1) << (2 * CB * b) | init_cell<MODEL>(o.v3) << (2 * CB * b + CB);
+            even = init_next<MODEL>(init_next<MODEL>(even, o.v2), o.v0);
+            odd = init_next<MODEL>(init_next<MODEL>(odd, o.v3), o.v1);
         }
+        even = init_word<MODEL>(even);
+        odd = init_word<MODEL>(odd);
         planes[g] = (y & 1) ? odd : even;
         planes[total + g] = (y & 1) ? even : odd;
     }
