@@ -303,6 +303,7 @@ __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p
             bmid = bdn;
         }
     }
+    int64_t bonds = (int64_t)nz - 2 * (int64_t)diff;
     if (MODEL == 0) {
         // n_1 .. n_4 from the sums of sd_add_ising4 (t = 8 - 2 d); the
         // thread's cells were 16 per word pair, the rest of the histogram
@@ -313,10 +314,8 @@ __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p
         hist[6] = e[1] - e[2];
         hist[4] = e[0] - e[1] - e[2] - e[3];
         hist[8] = cells - hist[6] - hist[4] - hist[2] - hist[0];
-        nz = 2 * cells;
-        diff = 0;
         const uint32_t dsum = hist[6] + 2 * hist[4] + 3 * hist[2] + 4 * hist[0];
-        nz -= dsum;
+        bonds = (int32_t)(2 * cells - dsum);    // (a thread's share may be negative)
     }
     if (MODEL == 2) {
         // 1-bit cells are all +1 or -1; t = 4 is what the other bins leave
@@ -325,8 +324,7 @@ __global__ __launch_bounds__(256) void bmq_kernel(const uint32_t* __restrict__ p
     }
     // acc: [0] B, [1] M, [2] #(+1), [3] #(-1), [4] #(0), [5 + k] #(sigma h = k - 4);
     // invalid cells are what the three counts leave of L^2 (done on the host)
-    int64_t v[14] = {(int64_t)nz - 2 * (int64_t)diff, (int64_t)np1 - (int64_t)nm1, (int64_t)np1, (int64_t)nm1,
-                     (int64_t)n0};
+    int64_t v[14] = {bonds, (int64_t)np1 - (int64_t)nm1, (int64_t)np1, (int64_t)nm1, (int64_t)n0};
 #pragma unroll
     for (int k = 0; k < 9; ++k) v[5 + k] = (int64_t)hist[k];
     block_add<14>(v, acc, red);
