@@ -259,7 +259,9 @@ int group_sweep_noalloc(mcl_lattice* const* hs, int count, const int64_t* n,
  * Results never depend on it.
  *   rows_log2L[k] : band height (rows per thread: 8, 16, 32 or 64) for
  *                   lattices with 2^k <= L < 2^(k+1); a call with little
- *                   work for the chip takes shorter bands;
+ *                   work for the chip takes shorter bands (the environment
+ *                   variable MCL_GROUP_ROWS, 2 to 64 and read on each call,
+ *                   sets the most that a call takes instead);
  *   use_graph     : replay repeated call shapes from captured graphs;
  *   largest_first : order each launch's tile list by decreasing L (else
  *                   call order);
@@ -279,6 +281,11 @@ typedef struct mcl_group_tuning {
 } mcl_group_tuning;
 int mcl_group_tuning_get(mcl_group_tuning* out);
 int mcl_group_tuning_set(const mcl_group_tuning* in);   /* MCL_EARG on a value out of range */
+/* The band heights that group_sweep plans, under the present tuning, for a
+ * call whose `count` entries (model and linear size) all have work: rows per
+ * thread, or 0 for a lattice that is held in LDS or swept on its own.
+ * Needs no GPU.  MCL_EARG, MCL_EMODEL or MCL_EL on a bad argument. */
+int mcl_group_rows(int count, const int* model, const int64_t* L, int32_t* rows);
 
 /* Release a handle (does not free the caller's device memory).  Waits for
  * the handle's stream first, so the buffer is free for reuse on return,

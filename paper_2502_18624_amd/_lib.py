@@ -74,6 +74,7 @@ SIGNATURES = {
                                    ctypes.POINTER(_DBL)]),
     "mcl_group_tuning_get": (_INT, [ctypes.POINTER(GroupTuning)]),
     "mcl_group_tuning_set": (_INT, [ctypes.POINTER(GroupTuning)]),
+    "mcl_group_rows": (_INT, [_INT, ctypes.POINTER(_INT), ctypes.POINTER(_I64), ctypes.POINTER(_I32)]),
     "lattice_free": (_INT, [_P]),
     "mcl_strerror": (ctypes.c_char_p, [_INT]),
     "mcl_last_hip_error": (_INT, []),

@@ -33,6 +33,17 @@ def set_tuning(t: GroupTuning) -> None:
     check(lib().mcl_group_tuning_set(ctypes.byref(t)), "mcl_group_tuning_set")
 
 
+def planned_rows(shapes) -> list:
+    """Band heights that group_sweep plans for replicas of these (model, L)
+    under the present tuning; 0 where a replica takes no batched launch."""
+    shapes = [(int(m), int(L)) for m, L in shapes]
+    k = len(shapes)
+    rows = (ctypes.c_int32 * k)()
+    check(lib().mcl_group_rows(k, (ctypes.c_int * k)(*(m for m, _ in shapes)),
+                               (ctypes.c_int64 * k)(*(L for _, L in shapes)), rows), "mcl_group_rows")
+    return list(rows)
+
+
 FIELDS = ("use_graph", "largest_first", "wg_per_cu", "split_models", "graph_sweeps")
 # candidate values of the scalar fields, searched after the band heights
 CHOICES = {"wg_per_cu": (0, 2, 4, 8), "split_models": (0, 1), "use_graph": (0, 1), "largest_first": (0, 1)}

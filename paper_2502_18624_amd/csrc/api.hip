@@ -331,32 +331,81 @@ bool resident_alone(const mcl_lattice* h, int64_t n)
 // of them 637 against 548.
 constexpr int kResidentMany = 128;
 constexpr size_t kResidentGroupLds = 76 * 1024;
-bool resident_small(const mcl_lattice* h) { return h->L <= (h->model == MCL_ISING_LUT ? 512 : 256); }
-bool resident_in_group(const mcl_lattice* h)
-{
-    return mcl::resident_lds(h->model, h->L) <= kResidentGroupLds;
-}
+
+// A replica of the batched launches as the plan of a call sees it (L = 0: not
+// one of theirs).
+struct Replica {
+    int model;
+    int64_t L;
+    int64_t vectors() const { return L / (model == MCL_ISING_LUT ? 256 : 64); }     // of a plane row
+    bool small() const { return L <= (model == MCL_ISING_LUT ? 512 : 256); }
+    bool fits() const { return mcl::resident_lds(model, L) <= kResidentGroupLds; }
+};
 
 // Sweeps of one resident launch (about 2 ms at L = 256).
 constexpr int64_t kResidentSweeps = 256;
 
-// Band height of a replica: the tuning's for its size, but at most `cap` rows
-// and few enough to fill a tile of 256 threads (at least 2).  A call whose
-// replicas give few threads needs the shorter bands as a single small lattice
-// does (band_rows in sweep.hip): the cap goes down from 64 until there are
+// The plan of a call: which of its replicas go resident, and the band heights of
+// the others -- the tuning's for their size, but at most `cap` rows and few
+// enough to fill a tile of 256 threads (at least 2).  A call whose replicas
+// give few threads needs the shorter bands as a single small lattice does
+// (band_rows in sweep.hip): the cap goes down from 64 until there are
 // kGroupThreads, since a launch of a few rounds of workgroups waits for its
 // last, partly filled one.  48 replicas of L = 512 .. 8192, 4 sweeps:
 // 2.02 ms, with 2^19 threads 2.29, 2^21 2.09, the tuning's bands 2.80.  1-bit
 // replicas take half the cap, as a row costs them twice as much and the last
 // tiles are waited for: 1.90 ms.
+// The environment variable MCL_GROUP_ROWS (2 to 64, rounded down to a power of
+// two; read at every call) is the cap of every replica instead: calls that give
+// few threads then run the bands of those that give many, as a test does.
 constexpr int64_t kGroupThreads = int64_t(1) << 20;
-int64_t group_rows(const mcl_lattice* h, const mcl_group_tuning& tun, int64_t cap)
-{
-    if (h->model == MCL_ISING_LUT) cap = std::max<int64_t>(2, cap / 2);
-    int64_t rows = std::min<int64_t>(cap, tun.rows_log2L[log2_floor(h->L)]);
-    while (rows > 2 && h->g.Q * (h->L / rows) < 256) rows >>= 1;
-    return rows;
-}
+struct GroupRule {
+    bool res_many = false, res_all = false, forced = false;
+    int64_t cap = 128;
+    const mcl_group_tuning& tun;
+    // at(i): replica i of `count`
+    template <class At>
+    GroupRule(const mcl_group_tuning& t, int count, const At& at) : tun(t)
+    {
+        // every one that fits, if they are many; or all of a call's, if each is
+        // small enough to do so alone
+        int fit = 0, small = 0, all = 0;
+        for (int i = 0; i < count; ++i) {
+            const Replica r = at(i);
+            if (r.L == 0) continue;
+            ++all;
+            fit += r.fits();
+            small += r.small();
+        }
+        res_many = fit >= kResidentMany;
+        res_all = small == all;
+        if (const char* e = std::getenv("MCL_GROUP_ROWS")) {
+            const long long v = std::atoll(e);
+            if (v >= 2 && v <= 64) {
+                forced = true;
+                cap = int64_t(1) << log2_floor(v);
+                return;
+            }
+        }
+        for (int64_t threads = 0; cap > 2 && threads < kGroupThreads;) {
+            cap >>= 1;
+            threads = 0;
+            for (int i = 0; i < count; ++i) {
+                const Replica r = at(i);
+                if (r.L != 0 && !resident(r)) threads += r.vectors() * (r.L / rows(r));
+            }
+        }
+    }
+    bool resident(const Replica& r) const { return res_all || (res_many && r.fits()); }
+    int64_t rows(const Replica& r) const
+    {
+        int64_t most = cap;
+        if (r.model == MCL_ISING_LUT && !forced) most = std::max<int64_t>(2, cap / 2);
+        int64_t rows = std::min<int64_t>(most, tun.rows_log2L[log2_floor(r.L)]);
+        while (rows > 2 && r.vectors() * (r.L / rows) < 256) rows >>= 1;
+        return rows;
+    }
+};
 
 // Cost of a 16-byte vector by model: the VALU instructions of its updates (32
 // of 14.8 and 18 for 4-bit cells, 128 of 7.55 for 1-bit cells).  The XCDs take
@@ -387,32 +436,16 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
                  const mcl_group_tuning& tun, int cus, GroupImage& img, void* host, int* order)
 {
     img = GroupImage();
-    // which replicas go resident: every one that fits, if they are many; or all
-    // of a call's, if each is small enough to do so alone
-    int fit = 0, small = 0, all = 0;
+    const auto replica = [&](int i) { return Replica{hs[i]->model, batched(hs[i], n[i]) ? hs[i]->L : 0}; };
+    const GroupRule rule(tun, count, replica);
     for (int i = 0; i < count; ++i)
         if (batched(hs[i], n[i])) {
-            ++all;
-            fit += resident_in_group(hs[i]);
-            small += resident_small(hs[i]);
-        }
-    const bool res_many = fit >= kResidentMany, res_all = small == all;
-    const auto is_res = [&](int i) { return (res_many && resident_in_group(hs[i])) || res_all; };
-    for (int i = 0; i < count; ++i)
-        if (batched(hs[i], n[i])) {
-            const bool res = is_res(i);
-            (res ? img.res_nmax : img.nmax) = std::max(res ? img.res_nmax : img.nmax, n[i]);
+            int64_t& most = rule.resident(replica(i)) ? img.res_nmax : img.nmax;
+            most = std::max(most, n[i]);
             img.ndesc++;
             img.nbc += hs[i]->model == MCL_BC;
             img.nlut += hs[i]->model == MCL_ISING_LUT;
         }
-    int64_t cap = 128;
-    for (int64_t threads = 0; cap > 2 && threads < kGroupThreads;) {
-        cap >>= 1;
-        threads = 0;
-        for (int i = 0; i < count; ++i)
-            if (batched(hs[i], n[i]) && !is_res(i)) threads += hs[i]->g.Q * (hs[i]->L / group_rows(hs[i], tun, cap));
-    }
     img.off_bc = align_up(img.ndesc * sizeof(mcl::GroupDesc), 256);
     img.off_lut = align_up(img.off_bc + img.nbc * 96 * sizeof(uint2), 256);
     img.off_s = align_up(img.off_lut + img.nlut * sizeof(mcl::LutRec), 256);
@@ -431,7 +464,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         const int m = !res && tun.split_models ? pass - 1 : -1;
         int cnt = 0;
         for (int i = 0; i < count; ++i)
-            if (batched(hs[i], n[i]) && is_res(i) == res && (m < 0 || hs[i]->model == m)) order[cnt++] = i;
+            if (batched(hs[i], n[i]) && rule.resident(replica(i)) == res && (m < 0 || hs[i]->model == m)) order[cnt++] = i;
         if (cnt == 0) continue;
         // decreasing L, call order among equal L (an in-place sort on the pair)
         if (res)
@@ -450,7 +483,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         for (int j = 0; j < cnt; ++j) {
             const int i = order[j];
             const mcl_lattice* h = hs[i];
-            const uint32_t rows = (uint32_t)group_rows(h, tun, cap);
+            const uint32_t rows = (uint32_t)rule.rows(replica(i));
             const int64_t threads = h->g.Q * (h->L / rows);
             ln.mask |= h->model == MCL_ISING ? mcl::kMaskIsing : h->model == MCL_BC ? mcl::kMaskBC : mcl::kMaskLut;
             if (res) {
@@ -497,7 +530,7 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         tiles = 0;
         for (int j = 0; j < cnt; ++j) {
             const mcl_lattice* h = hs[order[j]];
-            const int64_t rows = group_rows(h, tun, cap);
+            const int64_t rows = rule.rows(replica(order[j]));
             const uint64_t one = (uint64_t)rows * kVectorCost[h->model];
             const uint64_t k = (uint64_t)((h->g.Q * (h->L / rows) + 255) / 256);
             for (; part < 8 && cost * part / 8 <= sum + k * one; ++part) share[part] = tiles + (cost * part / 8 - sum) / one;
@@ -1504,6 +1537,25 @@ int mcl_group_tuning_set(const mcl_group_tuning* in)
     if (!in || !valid_tuning(*in)) return MCL_EARG;
     std::lock_guard<std::mutex> lk(g_group_mu);
     g_tuning = *in;
+    return MCL_OK;
+}
+
+int mcl_group_rows(int count, const int* model, const int64_t* L, int32_t* rows)
+{
+    if (count < 0 || (count > 0 && (!model || !L || !rows))) return MCL_EARG;
+    for (int i = 0; i < count; ++i) {
+        if (!valid_model(model[i])) return MCL_EMODEL;
+        if (!valid_L(model[i], L[i])) return MCL_EL;
+    }
+    std::lock_guard<std::mutex> lk(g_group_mu);
+    const auto replica = [&](int i) { return Replica{model[i], L[i] <= kGroupMaxL ? L[i] : 0}; };
+    const GroupRule rule(g_tuning, count, replica);
+    int some = 0;
+    for (int i = 0; i < count; ++i) some += replica(i).L != 0;
+    for (int i = 0; i < count; ++i) {
+        const Replica r = replica(i);
+        rows[i] = some < 2 || r.L == 0 || rule.resident(r) ? 0 : (int32_t)rule.rows(r);
+    }
     return MCL_OK;
 }
 
