@@ -92,7 +92,8 @@ def autotune_group(shapes, sweeps_per_call=8, reps=2, beta=0.44, D=0.5, verbose=
 
     from .lattice import Lattice
 
-    mix = sorted(Counter((int(m), int(L)) for m, L in shapes).items())
+    shapes = [(int(m), int(L)) for m, L in shapes]
+    mix = sorted(Counter(shapes).items())
     key = json.dumps([torch.cuda.get_device_name(), mix, int(sweeps_per_call)])
     if cache_file and not _cache and os.path.exists(cache_file):
         try:
@@ -112,7 +113,13 @@ def autotune_group(shapes, sweeps_per_call=8, reps=2, beta=0.44, D=0.5, verbose=
     cur = get_tuning()
     best_t = _time_group(lats, sweeps_per_call, betas, Ds, reps)
     buckets = sorted(set(_log2(L) for (_, L), _ in mix))
-    # coordinate search: band height per size bucket, then graph, then order
+    # coordinate search: band height per size bucket, then graph, then order.
+    # A call caps its heights by the threads it gives, so several settings may
+    # plan the same bands: each plan is timed once, and where none differs the
+    # setting stays as it is (noise would choose it, for every later call).  A
+    # call without batched launches has nothing to search.
+    plan = planned_rows(shapes)
+    plans = {tuple(plan)}
     for b in buckets:
         for r in ROWS:
             if r == cur.rows_log2L[b]:
@@ -120,13 +127,17 @@ def autotune_group(shapes, sweeps_per_call=8, reps=2, beta=0.44, D=0.5, verbose=
             cand = tuning_from_dict(tuning_dict(cur))
             cand.rows_log2L[b] = r
             set_tuning(cand)
+            rows = tuple(planned_rows(shapes))
+            if rows in plans:
+                continue
+            plans.add(rows)
             el = _time_group(lats, sweeps_per_call, betas, Ds, reps)
             if verbose:
                 print("  rows[2^%d]=%d: %.3f ms" % (b, r, el * 1e3))
             if el < best_t:
                 best_t, cur = el, cand
     for field, values in CHOICES.items():
-        for v in values:
+        for v in values if any(plan) else ():
             if v == getattr(cur, field):
                 continue
             cand = tuning_from_dict(tuning_dict(cur))
