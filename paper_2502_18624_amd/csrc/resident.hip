@@ -245,13 +245,14 @@ __device__ __forceinline__ void resident(ResidentLds& tabs, const GroupDesc& d, 
     run_resident<MODEL, WORDS>(lds, reinterpret_cast<uint32_t*>(B), d.plane0, L, t, n, rule);
 }
 
-// One lattice, its tables passed by value.
-template <int MODEL, bool WORDS>
+// One lattice, its tables passed by value; word by word, as its vectors are too
+// few for 1024 threads (L = 64 1.2 us a sweep, by vectors 2.5).
+template <int MODEL>
 __global__ __launch_bounds__(kMaxThreads) void resident_kernel(GroupDesc d, uint32_t n, BCTable bc, LutTable lt)
 {
     __shared__ ResidentLds tabs;
     if (MODEL == 1) dev::load_bc_table(tabs.bc, bc);
-    resident<MODEL, WORDS>(tabs, d, d.t0, n, lt);
+    resident<MODEL, true>(tabs, d, d.t0, n, lt);
 }
 
 // Sweeps [s0, min(s1, n)) of one descriptor per workgroup, any mix of models:
@@ -513,24 +514,15 @@ size_t resident_lds(int model, int64_t L)
     return model == 2 ? (size_t)(L * L / 8) + (size_t)kLutBucketBytes : (size_t)(L * L / 2);
 }
 
-// A single lattice word by word while its vectors are too few for 1024
-// threads: L = 64 1.2 us a sweep (by vectors 2.5), L = 192 5.5 (5.8).
-static bool by_words(int model, int64_t L) { return L * L / (model == 2 ? 256 : 64) <= 576; }
-
 hipError_t launch_resident(const GroupDesc& d, uint32_t n, const BCTable& bc, const LutTable& lt, hipStream_t s)
 {
     const int model = (int)d.model;
-    const int64_t L = d.L, vecs = L * L / (model == 2 ? 256 : 64);
-    const bool words = by_words(model, L);
-    const size_t props = words && model == 1 ? (size_t)(2 * L * row_blocks((uint32_t)(L >> 6)) * 16) : 0;
+    const int64_t L = d.L, words = L * L / (model == 2 ? 64 : 16);
+    const size_t props = model == 1 ? (size_t)(2 * L * row_blocks((uint32_t)(L >> 6)) * 16) : 0;
     const size_t lds = resident_lds(model, L) + props;
-    const uint32_t threads = threads_of(words ? 4 * vecs : vecs, kMaxThreads);
-    const auto either = [&](auto by_word, auto by_vector) {
-        return words ? go(by_word, 1, threads, lds, s, d, n, bc, lt) : go(by_vector, 1, threads, lds, s, d, n, bc, lt);
-    };
-    if (model == 0) return either(resident_kernel<0, true>, resident_kernel<0, false>);
-    if (model == 1) return either(resident_kernel<1, true>, resident_kernel<1, false>);
-    return either(resident_kernel<2, true>, resident_kernel<2, false>);
+    const uint32_t threads = threads_of(words, kMaxThreads);
+    const auto run = [&](auto kernel) { return go(kernel, 1, threads, lds, s, d, n, bc, lt); };
+    return model == 0 ? run(resident_kernel<0>) : model == 1 ? run(resident_kernel<1>) : run(resident_kernel<2>);
 }
 
 hipError_t launch_group_resident(const GroupDesc* desc, int count, size_t lds, int64_t vectors, uint32_t s0, uint32_t s1,
