@@ -14,6 +14,7 @@
 
 #include "../../include/mcl.h"
 #include "internal.h"
+#include "pinned_pool.h"
 
 struct mcl_lattice {
     int model;
@@ -937,20 +938,11 @@ int sweep_checked(mcl_lattice* h, int64_t n, double beta, double D, bool allow_g
 
 // ---------------------------------------------------------------------------
 // Pinned host memory of one call.  Taking it from the runtime costs more than
-// a small measurement, so up to kPinnedKept buffers of at most kPinnedMost
-// bytes wait for the next call of any handle and thread; others go back to the
-// runtime when their call ends.  A buffer is handed on only after the stream
-// that wrote it was waited for.
+// a small measurement, so a few buffers wait for the next call
+// (pinned_pool.h); others go back to the runtime when their call ends.  A
+// buffer is handed on only after the stream that wrote it was waited for.
 // ---------------------------------------------------------------------------
-constexpr size_t kPinnedKept = 8, kPinnedMost = size_t(4) << 20;
-struct PinnedBuffer {
-    void* host = nullptr;
-    void* dev = nullptr;
-    size_t bytes = 0;
-    int device = 0;
-};
-std::mutex g_pinned_mu;
-std::vector<PinnedBuffer> g_pinned;
+mcl::PinnedPool g_pinned;
 
 class Pinned {
 public:
@@ -962,16 +954,8 @@ public:
         int device = 0;
         hipError_t e = hipGetDevice(&device);
         if (e != hipSuccess) return e;
-        {
-            std::lock_guard<std::mutex> lk(g_pinned_mu);
-            for (size_t i = 0; i < g_pinned.size(); ++i)
-                if (g_pinned[i].bytes >= bytes && g_pinned[i].device == device) {
-                    b_ = g_pinned[i];
-                    g_pinned.erase(g_pinned.begin() + i);
-                    return hipSuccess;
-                }
-        }
-        PinnedBuffer b;
+        if (g_pinned.take(bytes, device, b_)) return hipSuccess;
+        mcl::PinnedBuffer b;
         b.bytes = std::max<size_t>(bytes, 64 * 1024);
         b.device = device;
         e = hipHostMalloc(&b.host, b.bytes, hipHostMallocMapped);
@@ -989,24 +973,15 @@ public:
         if (!b_.host) return;
         // (a call that returned early may have left kernels that write here)
         const bool idle = hipStreamSynchronize(stream_) == hipSuccess;
-        if (idle && b_.bytes <= kPinnedMost) {
-            try {
-                std::lock_guard<std::mutex> lk(g_pinned_mu);
-                if (g_pinned.size() < kPinnedKept) {
-                    g_pinned.push_back(b_);
-                    return;
-                }
-            } catch (...) {
-            }
-        }
-        (void)hipHostFree(b_.host);
+        const mcl::PinnedBuffer out = idle ? g_pinned.give(b_) : b_;
+        if (out.host) (void)hipHostFree(out.host);
     }
     void* host() const { return b_.host; }
     void* device() const { return b_.dev; }
 
 private:
     hipStream_t stream_;
-    PinnedBuffer b_;
+    mcl::PinnedBuffer b_;
 };
 
 // Rows of spins through two pinned buffers in turn, kChunkBytes of rows at a
