@@ -194,7 +194,7 @@ size_t full_lds(int64_t L)
 
 }  // namespace
 
-bool full_fits(int64_t L) { return full_lds(L) <= 160u * 1024u; }
+bool full_fits(int64_t L) { return full_lds(L) <= kLdsBytes; }
 
 hipError_t launch_corr_full(const Geom& g, int64_t* Cx, int64_t* Cy, int64_t* acc, hipStream_t s)
 {
@@ -208,11 +208,8 @@ hipError_t launch_corr_full(const Geom& g, int64_t* Cx, int64_t* Cy, int64_t* ac
     const uint32_t per_y = std::max<uint32_t>(1, std::min<uint32_t>(512 / groups, (tasks + kWaves - 1) / kWaves));
     const size_t lds = full_lds(g.L);
     const auto go = [&](auto kernel) {
-        if (lds > 32u * 1024u) {
-            const hipError_t e =
-                hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
+        const hipError_t e = allow_lds(kernel, lds, kLdsBytes);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3(nx + groups * per_y), dim3(kThreads), lds, s, g.plane0, L, nx, per_y, Cx, Cy, acc);
         return hipGetLastError();
     };

@@ -19,6 +19,19 @@ struct Geom {
     int64_t plane_words() const { return L * W; }
 };
 
+// Lets launches of a kernel on the current device take `lds` bytes of dynamic
+// LDS where that is more than any launch may.  The limit belongs to the kernel,
+// so what is set is the most that any of its launches takes: threads that launch
+// it for lattices of different sizes at the same time set the same value.
+template <class K>
+hipError_t allow_lds(K kernel, size_t lds, size_t most)
+{
+    if (lds <= 32u * 1024u) return hipSuccess;
+    if (lds > most) return hipErrorInvalidValue;
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+}
+constexpr size_t kLdsBytes = 160 * 1024;    // of a workgroup
+
 // Write the initial state into both planes.
 hipError_t launch_init(const Geom& g, int model, int init_state, uint64_t seed, hipStream_t s);
 

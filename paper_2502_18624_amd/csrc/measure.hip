@@ -959,7 +959,7 @@ namespace {
 // multi-pass form at small L).
 size_t sx_lds_budget()
 {
-    size_t budget = 160u * 1024u;
+    size_t budget = kLdsBytes;
     if (const char* e = std::getenv("MCL_SX_LDS_BUDGET")) {
         const long long v = std::atoll(e);
         if (v > 0 && (size_t)v < budget) budget = (size_t)v;
@@ -987,12 +987,8 @@ hipError_t corr_sampled_x(const Geom& g, const SampledArgs& a, hipStream_t s)
     for (int j0 = 0; j0 < a.nr; j0 += max_r) {
         const int nr = std::min(max_r, a.nr - j0);
         const size_t lds = rowb * (1 + G);
-        // the attribute belongs to the current device: set it for every launch that needs it
-        if (lds > 64u * 1024u) {
-            e = hipFuncSetAttribute((const void*)corr_sxb_kernel<MODEL>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds);
-            if (e != hipSuccess) return e;
-        }
+        e = allow_lds(corr_sxb_kernel<MODEL>, lds, kLdsBytes);
+        if (e != hipSuccess) return e;
         for (uint32_t rho0 = 0; rho0 < 16; rho0 += G) {
             hipLaunchKernelGGL((corr_sxb_kernel<MODEL>), dim3(gx), dim3(kSxThreads), lds, s, g.plane0, a.rbits, L, a.r + j0, nr, rho0,
                                G, a.Cx + j0);
@@ -1008,13 +1004,11 @@ hipError_t corr_sampled_y(const Geom& g, int model, const SampledArgs& a, hipStr
     const uint32_t L = (uint32_t)g.L, NS = L / 16;
     if ((L & (L - 1)) != 0 || L < 64) return hipErrorInvalidValue;
     const size_t need = (model == 1 ? 2 : 1) * (size_t)(NS + NS / 2) * 4;
-    const bool staged = need <= 152u * 1024u;             // with the kernel's own arrays, a workgroup's 160 KiB
+    constexpr size_t kMost = 152 * 1024;                  // with the kernel's own arrays, a workgroup's 160 KiB
+    const bool staged = need <= kMost;
     const auto go = [&](auto kernel) {
-        if (staged && need > 32u * 1024u) {
-            const hipError_t e =
-                hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-            if (e != hipSuccess) return e;
-        }
+        const hipError_t e = allow_lds(kernel, staged ? need : 0, kMost);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3(16u * (uint32_t)tbits_words(L)), dim3(kYThreads), staged ? need : 0, s, a.tbits, L,
                            a.r, a.nr, a.Cy);
         return hipGetLastError();

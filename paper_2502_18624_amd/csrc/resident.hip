@@ -24,6 +24,9 @@ namespace {
 // 750).
 constexpr uint32_t kMaxThreads = 1024;
 
+// Dynamic LDS of a launch, beside the kernels' tables.
+constexpr size_t kMostLds = 150 * 1024;
+
 // The largest lattices that trapezoid launches are for, us per sweep at 32
 // sweeps, against one launch per half-sweep: L = 7168 27.6 against about 29,
 // L = 8192 33.6 against 33.9 and 34.7 against 34.0 at three sweeps; 1-bit
@@ -431,11 +434,8 @@ uint32_t threads_of(int64_t vectors, int64_t most)
 template <class K, class... A>
 hipError_t go(K kernel, uint32_t grid, uint32_t threads, size_t lds, hipStream_t s, A... args)
 {
-    if (lds > 32u * 1024u) {
-        const hipError_t e =
-            hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = allow_lds(kernel, lds, kMostLds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, args...);
     return hipGetLastError();
 }
@@ -467,7 +467,7 @@ int64_t trapezoid_sweeps(const Geom& g)
     // four; three where that gives more tiles for the compute units (L = 3008:
     // 9.5 us a sweep, with four 10.1)
     const int64_t m = g.cb == 4 && g.L > 1536 && g.L < 4096 ? 3 : 4;
-    return trapezoid_lds(g, 2 * m) <= 150u * 1024u ? m : 0;
+    return trapezoid_lds(g, 2 * m) <= kMostLds ? m : 0;
 }
 
 hipError_t launch_trapezoids(const Geom& g, int model, int64_t sweeps, uint32_t t, uint64_t seed,
