@@ -8,7 +8,6 @@
 #include <map>
 #include <mutex>
 #include <new>
-#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -380,6 +379,7 @@ struct GroupRule {
         }
         res_many = fit >= kResidentMany;
         res_all = small == all;
+        if (res_all || (res_many && fit == all)) return;        // (no bands to plan)
         if (const char* e = std::getenv("MCL_GROUP_ROWS")) {
             const long long v = std::atoll(e);
             if (v >= 2 && v <= 64) {
@@ -463,22 +463,23 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
     for (int pass = 0; pass < (tun.split_models ? 4 : 2); ++pass) {
         const bool res = pass == 0;
         const int m = !res && tun.split_models ? pass - 1 : -1;
+        if ((res ? img.res_nmax : img.nmax) == 0) continue;
         int cnt = 0;
         for (int i = 0; i < count; ++i)
             if (batched(hs[i], n[i]) && rule.resident(replica(i)) == res && (m < 0 || hs[i]->model == m)) order[cnt++] = i;
         if (cnt == 0) continue;
-        // decreasing L, call order among equal L (an in-place sort on the pair)
-        if (res)
-            // resident ones by cost, models together: workgroup ids go round
-            // the XCDs, which would otherwise divide alternating models
-            // among them
-            std::sort(order, order + cnt, [&](int a, int b) {
-                const auto key = [&](int i) { return std::make_tuple(-hs[i]->L, hs[i]->model != MCL_BC, hs[i]->model, i); };
-                return key(a) < key(b);
-            });
-        else if (tun.largest_first)
-            std::sort(order, order + cnt,
-                      [&](int a, int b) { return hs[a]->L != hs[b]->L ? hs[a]->L > hs[b]->L : a < b; });
+        // decreasing L, call order among equal L; resident ones by cost, models
+        // together: workgroup ids go round the XCDs, which would otherwise
+        // divide alternating models among them.  (In place, and only where the
+        // order is written and not there yet: the plan is host time of every call.)
+        const auto before = [&](int a, int b) {
+            constexpr int kRank[3] = {1, 0, 2};
+            if (hs[a]->L != hs[b]->L) return hs[a]->L > hs[b]->L;
+            if (res && hs[a]->model != hs[b]->model) return kRank[hs[a]->model] < kRank[hs[b]->model];
+            return a < b;
+        };
+        if (base && (res || tun.largest_first) && !std::is_sorted(order, order + cnt, before))
+            std::sort(order, order + cnt, before);
         GroupLaunch ln{0, k, cnt, 0, 0};
         uint64_t tiles = 0, cost = 0;
         for (int j = 0; j < cnt; ++j) {

@@ -175,7 +175,10 @@ hipError_t launch_group_half(int mask, int color, const GroupDesc* desc, int cou
 // single lattice with its tables by value, or sweeps [s0, min(s1, n)) of
 // `count` descriptors of any models, at most `lds` bytes and `vectors` 16-byte
 // vectors of a plane each.
-size_t resident_lds(int model, int64_t L);
+inline size_t resident_lds(int model, int64_t L)
+{
+    return model == 2 ? (size_t)(L * L / 8) + (size_t)kLutBucketBytes : (size_t)(L * L / 2);
+}
 hipError_t launch_resident(const GroupDesc& d, uint32_t n, const BCTable& bc, const LutTable& lt, hipStream_t s);
 hipError_t launch_group_resident(const GroupDesc* desc, int count, size_t lds, int64_t vectors, uint32_t s0, uint32_t s1,
                                  const uint2* bc_tables, const LutRec* luts, hipStream_t s);

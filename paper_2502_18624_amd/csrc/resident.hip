@@ -509,11 +509,6 @@ hipError_t launch_half_words(const Geom& g, int model, int color, uint32_t t, ui
     return model == 0 ? run(half_words_kernel<0>) : model == 1 ? run(half_words_kernel<1>) : run(half_words_kernel<2>);
 }
 
-size_t resident_lds(int model, int64_t L)
-{
-    return model == 2 ? (size_t)(L * L / 8) + (size_t)kLutBucketBytes : (size_t)(L * L / 2);
-}
-
 hipError_t launch_resident(const GroupDesc& d, uint32_t n, const BCTable& bc, const LutTable& lt, hipStream_t s)
 {
     const int model = (int)d.model;
