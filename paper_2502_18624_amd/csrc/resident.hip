@@ -64,7 +64,7 @@ __device__ __forceinline__ void update_vector(const Rule& u, char* own, const ch
     if (MODEL == 0) {
         *at = dev::ising_vec<0>(src, a, b, mid, halo, odd, kv >> 2, 0u, t, c, u.k0, u.k1, 0u, u.T4, u.T8);
     } else if (MODEL == 2) {
-        *at = dev::lut_vec<0, true>(src, a, b, mid, halo, odd, kv, t, c, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
+        *at = dev::lut_vec<0>(src, a, b, mid, halo, odd, kv, t, c, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
     } else {
         const Philox4 p = philox4x32_10(kv >> 7, 0u, t, 2u + c, u.k0, u.k1);
         *at = dev::bc_vec<0>(src, a, b, mid, halo, odd, kv >> 2, 0u, philox_word(p, (int)((kv >> 5) & 3)), t, c, u.k0,
@@ -139,9 +139,9 @@ __device__ __forceinline__ void update_word(const Rule& u, char* own, const char
         const uint32_t eq4 = ~(d0 | d1 | d2 | d3), eq3 = (t1 ^ t2) & ~(u1 | u2);
         const auto draw = [&](uint32_t stream) {
             if (!EXACT)
-                return dev::lut_word_fast<0, true>(kv >> 2, t, stream, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
+                return dev::lut_word_fast<0>(kv >> 2, t, stream, u.k0, u.k1, 0u, u.buckets, u.lut, u.T8, u.kmax);
             const uint32_t blk = kv >> 4;
-            return dev::lut_word_loop(philox4x32_10(blk, 0u, t, stream, u.k0, u.k1),
+            return dev::lut_word(philox4x32_10(blk, 0u, t, stream, u.k0, u.k1),
                                  philox4x32_10(blk + 1, 0u, t, stream, u.k0, u.k1), u.lut, u.T8, u.kmax);
         };
         const uint32_t e4 = draw(8u + 2u * c), e8 = draw(9u + 2u * c) & e4;

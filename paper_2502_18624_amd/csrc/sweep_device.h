@@ -440,10 +440,13 @@ __device__ __forceinline__ uint32_t lut_lookup(const uint32_t* __restrict__ T, u
 }
 
 // Random bits of 32 cells (8 groups of 4) from the 8 draws of two Philox
-// blocks P, R, by the exact table search: eight independent chains.  It is run
-// below 0.63 T_c only, but there by up to 31% of a wave's words per stream: four
-// sweeps of L = 16384 at T_c / 2 take 348 us, with the loop below 408 (257 at
-// T_c either way); of 64 batched replicas of L = 4096 1.34 against 1.55 ms.
+// blocks P, R, by the exact table search: eight independent chains.  Below
+// 0.63 T_c up to 31% of a wave's words per stream take it.  As a loop, which is
+// one serial chain of table reads but half the code, it cost, at T_c / 2, four
+// sweeps of L = 16384 408 us against 348 (257 at T_c either way), 32 of L = 4096
+// in LDS 495 against 354 (268 at T_c), 64 batched replicas of L = 4096 1.55 ms
+// against 1.34; at T_c the loop gains 1% in LDS at L = 256, and a single sweep a
+// word per thread, which takes no other search, loses: 10.0 against 7.0 us.
 __device__ __forceinline__ uint32_t lut_word(const Philox4& P, const Philox4& R, const uint32_t* __restrict__ T,
                                              uint32_t T8, uint32_t kmax)
 {
@@ -451,21 +454,6 @@ __device__ __forceinline__ uint32_t lut_word(const Philox4& P, const Philox4& R,
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         w |= lut_lookup(T, T8, kmax, philox_word(j < 4 ? P : R, j & 3)) << (4 * j);
-    return w;
-}
-
-// The same as a loop, one serial chain of table reads, for the kernels that hold
-// their rows in LDS: their code, in several copies, would be half this search.
-__device__ __forceinline__ uint32_t lut_word_loop(Philox4 P, Philox4 R, const uint32_t* __restrict__ T, uint32_t T8,
-                                                  uint32_t kmax)
-{
-    uint32_t w = 0;
-#pragma unroll 1
-    for (int j = 0; j < 8; ++j) {
-        w = (w >> 4) | (lut_lookup(T, T8, kmax, P.v0) << 28);
-        P = Philox4{P.v1, P.v2, P.v3, R.v0};
-        R = Philox4{R.v1, R.v2, R.v3, 0u};
-    }
     return w;
 }
 
@@ -512,8 +500,7 @@ __device__ __forceinline__ void lut_fast_draw(uint32_t u, const uint2* __restric
 
 // Random bits of the 32 cells whose 8 groups of 4 start at group g0 (a
 // multiple of 8): Philox blocks g0/4 and g0/4 + 1 of `stream`.
-// LOOP: the exact search as a loop.
-template <int HM, bool LOOP = false>
+template <int HM>
 __device__ __forceinline__ uint32_t lut_word_fast(uint64_t g0, uint32_t t, uint32_t stream, uint32_t k0, uint32_t k1,
                                                   uint32_t hu, const uint2* __restrict__ B,
                                                   const uint32_t* __restrict__ T, uint32_t T8, uint32_t kmax)
@@ -530,11 +517,11 @@ __device__ __forceinline__ uint32_t lut_word_fast(uint64_t g0, uint32_t t, uint3
     lut_fast_draw<5>(R.v1, B, w, flags);
     lut_fast_draw<6>(R.v2, B, w, flags);
     lut_fast_draw<7>(R.v3, B, w, flags);
-    if (flags >> 31) w = LOOP ? lut_word_loop(P, R, T, T8, kmax) : lut_word(P, R, T, T8, kmax);
+    if (flags >> 31) w = lut_word(P, R, T, T8, kmax);
     return w;
 }
 
-template <int HM, bool LOOP = false>
+template <int HM>
 __device__ __forceinline__ uint4 lut_vec(const uint4& src, const uint4& up, const uint4& dn, const uint4& mid,
                                          uint32_t halo, bool odd, uint64_t kv, uint32_t t, uint32_t color,
                                          uint32_t k0, uint32_t k1, uint32_t hu, const uint2* __restrict__ B,
@@ -552,8 +539,8 @@ __device__ __forceinline__ uint4 lut_vec(const uint4& src, const uint4& up, cons
         const uint32_t eq4 = ~(b0 | b1 | b2 | b3);
         const uint32_t eq3 = (t1 ^ t2) & ~(u1 | u2);
         const uint64_t g0 = (kv + 32u * d) >> 2;
-        const uint32_t e4 = lut_word_fast<HM, LOOP>(g0, t, 8u + 2u * color, k0, k1, hu, B, T, T8, kmax);
-        const uint32_t e8 = lut_word_fast<HM, LOOP>(g0, t, 9u + 2u * color, k0, k1, hu, B, T, T8, kmax) & e4;
+        const uint32_t e4 = lut_word_fast<HM>(g0, t, 8u + 2u * color, k0, k1, hu, B, T, T8, kmax);
+        const uint32_t e8 = lut_word_fast<HM>(g0, t, 9u + 2u * color, k0, k1, hu, B, T, T8, kmax) & e4;
         // a spin keeps its value only when four neighbours agree and its
         // e^{-8 beta} bit is clear, or three agree and its e^{-4 beta} bit is clear
         const uint32_t keep = (eq4 & ~e8) | (eq3 & ~e4);

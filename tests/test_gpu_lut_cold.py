@@ -47,29 +47,46 @@ def test_cold_bands(mcl, fraction, group):
         lat.free()
 
 
+@pytest.mark.parametrize("L,ns", [(256, (1, 5)), (512, (4, 7)), (1536, (1, 6)), (4352, (4,))])
+def test_cold_rows_in_lds(mcl, L, ns):
+    """A word per thread, a whole lattice and tiles of rows in LDS."""
+    print("cold rows in LDS", L, flush=True)
+    beta, t = 2 * BETA_C, 0
+    lat = mcl.Lattice(LUT, L, 6150 + L)
+    want = oracle.init(LUT, L, 6150 + L)
+    for n in ns:
+        lat.sweep(n, beta)
+        oracle.sweep(want, LUT, 6150 + L, t, n, beta, 0.0, nthreads=16)
+        t += n
+        assert np.array_equal(lat.read(), want), n
+    lat.free()
+
+
 def test_what_the_exact_search_costs(mcl):
     """A word of 32 cells is about 242 VALU instructions; the search, 8 x 16
     instructions in eight independent chains, by 31% of them in each of two
     streams adds 79: a third.  As one serial chain of 8 x 26 it would be 129
     and the latency of 24 table reads in a row.  Both temperatures in turn, in
-    one process; the bound is half as much again."""
+    one process; the bound is half as much again.  A launch per half-sweep (one
+    sweep of L = 8192) and several sweeps of rows in LDS (32 of L = 4096)."""
     import torch
     print("cost of the exact search", flush=True)
-    lat = mcl.Lattice(LUT, 8192, 6200)
+    for L, n, calls in ((8192, 1, 100), (4096, 32, 10)):
+        lat = mcl.Lattice(LUT, L, 6200)
 
-    def once(beta):
-        torch.cuda.synchronize()
-        a = time.perf_counter()
-        for _ in range(100):
-            lat.sweep(1, beta)
-        torch.cuda.synchronize()
-        return time.perf_counter() - a
+        def once(beta):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            for _ in range(calls):
+                lat.sweep(n, beta)
+            torch.cuda.synchronize()
+            return (time.perf_counter() - a) / calls * 1e6
 
-    once(BETA_C)
-    warm, cold = [], []
-    for _ in range(8):
-        warm.append(once(BETA_C))
-        cold.append(once(2 * BETA_C))
-    lat.free()
-    print("us a sweep", min(warm) * 1e4, min(cold) * 1e4, flush=True)
-    assert min(cold) < 1.5 * min(warm)
+        once(BETA_C)
+        warm, cold = [], []
+        for _ in range(8):
+            warm.append(once(BETA_C))
+            cold.append(once(2 * BETA_C))
+        lat.free()
+        print(L, n, "us a call at T_c", min(warm), "at T_c / 2", min(cold), flush=True)
+        assert min(cold) < 1.5 * min(warm)
