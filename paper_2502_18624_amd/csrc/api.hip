@@ -802,7 +802,7 @@ hipError_t launch_sweeps(const mcl_lattice* h, const SweepParams& p, int64_t n, 
 {
     int64_t i = 0;
     const int64_t several = tbase || std::getenv("MCL_SWEEP_GRAPH") ? 0 : mcl::trapezoid_sweeps(h->g);
-    if (several && n > 1)
+    if (several && n >= mcl::trapezoid_least(h->g))
         for (int64_t runs = (n + several - 1) / several; runs > 0; --runs) {
             const int64_t m = (n - i + runs - 1) / runs;
             const hipError_t e = mcl::launch_trapezoids(h->g, h->model, m, t + (uint32_t)i, h->seed, p.T4, p.T8, p.tb,

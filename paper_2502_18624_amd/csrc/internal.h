@@ -183,8 +183,10 @@ hipError_t launch_resident(const GroupDesc& d, uint32_t n, const BCTable& bc, co
 hipError_t launch_group_resident(const GroupDesc* desc, int count, size_t lds, int64_t vectors, uint32_t s0, uint32_t s1,
                                  const uint2* bc_tables, const LutRec* luts, hipStream_t s);
 // Up to trapezoid_sweeps() sweeps (0: none) of one lattice in two launches, in
-// place, from sweep index t on; at least two.
+// place, from sweep index t on; at least two.  Worth it for calls of
+// trapezoid_least() sweeps or more.
 int64_t trapezoid_sweeps(const Geom& g);
+int64_t trapezoid_least(const Geom& g);
 hipError_t launch_trapezoids(const Geom& g, int model, int64_t sweeps, uint32_t t, uint64_t seed,
                              uint32_t T4, uint32_t T8, const BCTable& bc, const LutTable& lt, const void* buckets,
                              hipStream_t s);

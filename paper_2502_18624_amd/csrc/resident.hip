@@ -461,12 +461,31 @@ static size_t trapezoid_lds(const Geom& g, int64_t k)
     return (size_t)(2 * rows * g.Q * 16) + extra;
 }
 
+// Sizes at which the workgroups of a launch per half-sweep (2-row bands, 256
+// threads) just fill two or four rounds of the compute units, so that it is at
+// its best: 1 where only runs of two sweeps lose to it (time of two sweeps, and
+// five, against it: 4-bit L = 3904 .. 4096 1.00 .. 1.03, 0.96 .. 0.99; 1-bit
+// L = 11264 1.02, 1.00), 2 where all do (1-bit L = 11520 1.05, 1.04, four sweeps
+// 1.00), else 0 (L = 3840 0.97, 4160 0.86; 11008 0.98, 11776 0.84).
+static int full_rounds(const Geom& g)
+{
+    if (g.cb == 4) return g.L >= 3904 && g.L <= 4096 ? 1 : 0;
+    return g.L > 11264 && g.L <= 11520 ? 2 : g.L > 11008 && g.L <= 11264 ? 1 : 0;
+}
+
+int64_t trapezoid_least(const Geom& g) { return full_rounds(g) ? 3 : 2; }
+
 int64_t trapezoid_sweeps(const Geom& g)
 {
-    if (g.L < 128 || g.L > (g.cb == 1 ? kTrapezoidMaxLutL : kTrapezoidMaxL)) return 0;
-    // four; three where that gives more tiles for the compute units (L = 3008:
-    // 9.5 us a sweep, with four 10.1)
-    const int64_t m = g.cb == 4 && g.L > 1536 && g.L < 4096 ? 3 : 4;
+    if (g.L < 128 || g.L > (g.cb == 1 ? kTrapezoidMaxLutL : kTrapezoidMaxL) || full_rounds(g) == 2) return 0;
+    // Four: fewer launches.  Three have more tiles, L / 12 against L / 16, for the
+    // compute units, which 4-bit words gain from in between: us a sweep at 24
+    // sweeps, three against four, L = 1024 5.1 against 4.9, 1408 5.8 / 5.9, 1536
+    // 5.8 / 6.1 (Blume-Capel 7.2 / 7.7), 3008 9.1 / 9.8, 3584 10.8 / 11.2; 3648
+    // 11.5 / 11.6, where four sweeps take four in one run and three do not,
+    // 3904 12.6 / 12.4.  Two are nowhere better than three by more than 5% (L =
+    // 2048 6.6, 6.7), six at L <= 384 and from 6144 on, by up to 8% and 3%.
+    const int64_t m = g.cb == 4 && g.L >= 1536 && g.L <= 3584 ? 3 : 4;
     return trapezoid_lds(g, 2 * m) <= kMostLds ? m : 0;
 }
 
