@@ -232,12 +232,7 @@ bool valid_tuning(const mcl_group_tuning& t)
 std::mutex g_group_mu;
 mcl_group_tuning g_tuning = default_tuning();
 
-int log2_floor(int64_t v)
-{
-    int k = 0;
-    while ((int64_t(1) << (k + 1)) <= v) ++k;
-    return k;
-}
+int log2_floor(int64_t v) { return 63 - __builtin_clzll((unsigned long long)v); }
 
 // Blume-Capel table in the kernel's LDS order: 96 entries indexed
 // (n * 2 + b) * 16 + neighbour-cell-sum, x = threshold, y = always.
@@ -337,7 +332,7 @@ constexpr size_t kResidentGroupLds = 76 * 1024;
 struct Replica {
     int model;
     int64_t L;
-    int64_t vectors() const { return L / (model == MCL_ISING_LUT ? 256 : 64); }     // of a plane row
+    int64_t vectors() const { return L * L >> (model == MCL_ISING_LUT ? 8 : 6); }   // of a plane
     bool small() const { return L <= (model == MCL_ISING_LUT ? 512 : 256); }
     bool fits() const { return mcl::resident_lds(model, L) <= kResidentGroupLds; }
 };
@@ -361,51 +356,54 @@ constexpr int64_t kResidentSweeps = 256;
 constexpr int64_t kGroupThreads = int64_t(1) << 20;
 struct GroupRule {
     bool res_many = false, res_all = false, forced = false;
-    int64_t cap = 128;
-    const mcl_group_tuning& tun;
-    // at(i): replica i of `count`
+    int cap = 6;                        // log2 of its rows
+    int tuned[21];                      // of the tuning's
+
+    // at(i): replica i of `count`.  One pass over them (the plan is host time of
+    // every call): a band height divides a plane, so the threads at any cap follow
+    // from the vectors of the replicas by the most rows that each may take.
     template <class At>
-    GroupRule(const mcl_group_tuning& t, int count, const At& at) : tun(t)
+    GroupRule(const mcl_group_tuning& tun, int count, const At& at)
     {
-        // every one that fits, if they are many; or all of a call's, if each is
-        // small enough to do so alone
+        for (int k = 0; k < 21; ++k) tuned[k] = log2_floor(tun.rows_log2L[k]);
         int fit = 0, small = 0, all = 0;
+        int64_t sum[2][2][7] = {};      // vectors by [1-bit][fits()][most()]
         for (int i = 0; i < count; ++i) {
             const Replica r = at(i);
             if (r.L == 0) continue;
             ++all;
             fit += r.fits();
             small += r.small();
+            sum[r.model == MCL_ISING_LUT][r.fits()][most(r)] += r.vectors();
         }
+        // every one that fits, if they are many; or all of a call's, if each is
+        // small enough to do so alone
         res_many = fit >= kResidentMany;
         res_all = small == all;
-        if (res_all || (res_many && fit == all)) return;        // (no bands to plan)
         if (const char* e = std::getenv("MCL_GROUP_ROWS")) {
             const long long v = std::atoll(e);
             if (v >= 2 && v <= 64) {
                 forced = true;
-                cap = int64_t(1) << log2_floor(v);
+                cap = log2_floor(v);
                 return;
             }
         }
-        for (int64_t threads = 0; cap > 2 && threads < kGroupThreads;) {
-            cap >>= 1;
-            threads = 0;
-            for (int i = 0; i < count; ++i) {
-                const Replica r = at(i);
-                if (r.L != 0 && !resident(r)) threads += r.vectors() * (r.L / rows(r));
-            }
-        }
+        const auto threads = [&] {
+            int64_t t = 0;
+            for (int lut = 0; lut < 2; ++lut)
+                for (int fits = 0; fits < (res_many ? 1 : 2); ++fits)
+                    for (int m = 1; m < 7; ++m) t += sum[lut][fits][m] >> capped(m, lut != 0);
+            return t;
+        };
+        while (cap > 1 && threads() < kGroupThreads) --cap;
     }
     bool resident(const Replica& r) const { return res_all || (res_many && r.fits()); }
-    int64_t rows(const Replica& r) const
-    {
-        int64_t most = cap;
-        if (r.model == MCL_ISING_LUT && !forced) most = std::max<int64_t>(2, cap / 2);
-        int64_t rows = std::min<int64_t>(most, tun.rows_log2L[log2_floor(r.L)]);
-        while (rows > 2 && r.vectors() * (r.L / rows) < 256) rows >>= 1;
-        return rows;
-    }
+    int log2_rows(const Replica& r) const { return capped(most(r), r.model == MCL_ISING_LUT); }
+
+private:
+    // log2 of the rows that the tuning and the tiles leave a replica: 1 .. 6
+    int most(const Replica& r) const { return std::max(1, std::min(tuned[log2_floor(r.L)], log2_floor(r.vectors()) - 8)); }
+    int capped(int rows, bool lut) const { return std::max(1, std::min(rows, lut && !forced ? cap - 1 : cap)); }
 };
 
 // Cost of a 16-byte vector by model: the VALU instructions of its updates (32
@@ -429,34 +427,47 @@ mcl::GroupDesc describe(const mcl_lattice* h, int64_t n)
     return d;
 }
 
-// Plan the call (launches, tiles, grid) into `img`; when `host` is given,
-// also write the image there (it must hold img.bytes).  `order` is room for
-// `count` entry indices.  Allocates nothing.  MCL_ERANGE if a launch would
-// need more than 2^24 workgroups or 2^32 tiles.
-int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const double* beta, const double* D,
-                 const mcl_group_tuning& tun, int cus, GroupImage& img, void* host, int* order)
+// The replicas of a call, for its rule.
+struct Entries {
+    mcl_lattice* const* hs;
+    const int64_t* n;
+    Replica operator()(int i) const { return Replica{hs[i]->model, batched(hs[i], n[i]) ? hs[i]->L : 0}; }
+};
+
+// The sizes of a call's image.
+GroupImage group_size(mcl_lattice* const* hs, int count, const int64_t* n, const GroupRule& rule)
 {
-    img = GroupImage();
-    const auto replica = [&](int i) { return Replica{hs[i]->model, batched(hs[i], n[i]) ? hs[i]->L : 0}; };
-    const GroupRule rule(tun, count, replica);
-    for (int i = 0; i < count; ++i)
-        if (batched(hs[i], n[i])) {
-            int64_t& most = rule.resident(replica(i)) ? img.res_nmax : img.nmax;
-            most = std::max(most, n[i]);
-            img.ndesc++;
-            img.nbc += hs[i]->model == MCL_BC;
-            img.nlut += hs[i]->model == MCL_ISING_LUT;
-        }
+    GroupImage img;
+    const Entries at{hs, n};
+    for (int i = 0; i < count; ++i) {
+        const Replica r = at(i);
+        if (r.L == 0) continue;
+        int64_t& most = rule.resident(r) ? img.res_nmax : img.nmax;
+        most = std::max(most, n[i]);
+        img.ndesc++;
+        img.nbc += r.model == MCL_BC;
+        img.nlut += r.model == MCL_ISING_LUT;
+    }
     img.off_bc = align_up(img.ndesc * sizeof(mcl::GroupDesc), 256);
     img.off_lut = align_up(img.off_bc + img.nbc * 96 * sizeof(uint2), 256);
     img.off_s = align_up(img.off_lut + img.nlut * sizeof(mcl::LutRec), 256);
     img.bytes = img.off_s + 256;
-    char* base = (char*)host;
+    return img;
+}
+
+// Plan the call (launches, tiles, grid) into `img`, of group_size(), and write
+// the image to `base`, img.bytes of host memory.  `order` is room for `count`
+// entry indices.  Allocates nothing.  MCL_ERANGE if a launch would need more
+// than 2^24 workgroups or 2^32 tiles.
+int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const double* beta, const double* D,
+                 const mcl_group_tuning& tun, const GroupRule& rule, int cus, GroupImage& img, char* base, int* order)
+{
+    const Entries at{hs, n};
     // the sweep-offset word and the claim counters start at 0
-    if (base) std::memset(base + img.off_s, 0, 256);
+    std::memset(base + img.off_s, 0, 256);
     mcl::GroupDesc* hd = (mcl::GroupDesc*)base;
-    uint32_t* htab = base ? (uint32_t*)(base + img.off_bc) : nullptr;
-    mcl::LutRec* hlut = base ? (mcl::LutRec*)(base + img.off_lut) : nullptr;
+    uint32_t* htab = (uint32_t*)(base + img.off_bc);
+    mcl::LutRec* hlut = (mcl::LutRec*)(base + img.off_lut);
     size_t k = 0, nb = 0, nl = 0;
     // the resident replicas first, then the batched ones (model by model with
     // split_models)
@@ -465,60 +476,56 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         const int m = !res && tun.split_models ? pass - 1 : -1;
         if ((res ? img.res_nmax : img.nmax) == 0) continue;
         int cnt = 0;
-        for (int i = 0; i < count; ++i)
-            if (batched(hs[i], n[i]) && rule.resident(replica(i)) == res && (m < 0 || hs[i]->model == m)) order[cnt++] = i;
+        for (int i = 0; i < count; ++i) {
+            const Replica r = at(i);
+            if (r.L != 0 && rule.resident(r) == res && (m < 0 || r.model == m)) order[cnt++] = i;
+        }
         if (cnt == 0) continue;
         // decreasing L, call order among equal L; resident ones by cost, models
         // together: workgroup ids go round the XCDs, which would otherwise
-        // divide alternating models among them.  (In place, and only where the
-        // order is written and not there yet: the plan is host time of every call.)
+        // divide alternating models among them
         const auto before = [&](int a, int b) {
             constexpr int kRank[3] = {1, 0, 2};
             if (hs[a]->L != hs[b]->L) return hs[a]->L > hs[b]->L;
             if (res && hs[a]->model != hs[b]->model) return kRank[hs[a]->model] < kRank[hs[b]->model];
             return a < b;
         };
-        if (base && (res || tun.largest_first) && !std::is_sorted(order, order + cnt, before))
+        if ((res || tun.largest_first) && !std::is_sorted(order, order + cnt, before))
             std::sort(order, order + cnt, before);
         GroupLaunch ln{0, k, cnt, 0, 0};
         uint64_t tiles = 0, cost = 0;
         for (int j = 0; j < cnt; ++j) {
             const int i = order[j];
             const mcl_lattice* h = hs[i];
-            const uint32_t rows = (uint32_t)rule.rows(replica(i));
-            const int64_t threads = h->g.Q * (h->L / rows);
+            const int log2_rows = rule.log2_rows(at(i));
+            const int64_t threads = at(i).vectors() >> log2_rows;
             ln.mask |= h->model == MCL_ISING ? mcl::kMaskIsing : h->model == MCL_BC ? mcl::kMaskBC : mcl::kMaskLut;
             if (res) {
                 img.res_lds = std::max(img.res_lds, mcl::resident_lds(h->model, h->L));
                 img.res_vectors = std::max(img.res_vectors, h->g.Q * h->L);
                 img.res_lut += h->model == MCL_ISING_LUT;
             }
-            if (base) {
-                mcl::GroupDesc d = describe(h, n[i]);
-                d.rows = rows;
-                d.tile_begin = (uint32_t)tiles;
-                if (h->model == MCL_ISING) {
-                    ising_thresholds(beta[i], d.T4, d.T8);
-                } else if (h->model == MCL_BC) {
-                    d.tab = (uint32_t)nb;
-                    bc_lds_table(beta[i], D[i], htab + nb * 192);
-                } else {
-                    d.tab = (uint32_t)nl;
-                    const mcl::LutTable lt = lut_device_table(beta[i]);
-                    mcl::LutRec r;
-                    std::memset(&r, 0, sizeof(r));
-                    r.buckets = (uint2*)h->lutb;
-                    std::memcpy(r.T, lt.T, sizeof(r.T));
-                    r.kmax = lt.kmax;
-                    hlut[nl] = r;
-                }
-                hd[k] = d;
+            mcl::GroupDesc d = describe(h, n[i]);
+            d.rows = 1u << log2_rows;
+            d.tile_begin = (uint32_t)tiles;
+            if (h->model == MCL_ISING) {
+                ising_thresholds(beta[i], d.T4, d.T8);
+            } else if (h->model == MCL_BC) {
+                d.tab = (uint32_t)nb;
+                bc_lds_table(beta[i], D[i], htab + nb++ * 192);
+            } else {
+                d.tab = (uint32_t)nl;
+                const mcl::LutTable lt = lut_device_table(beta[i]);
+                mcl::LutRec r;
+                std::memset(&r, 0, sizeof(r));
+                r.buckets = (uint2*)h->lutb;
+                std::memcpy(r.T, lt.T, sizeof(r.T));
+                r.kmax = lt.kmax;
+                hlut[nl++] = r;
             }
-            nb += h->model == MCL_BC;
-            nl += h->model == MCL_ISING_LUT;
-            ++k;
+            hd[k++] = d;
             tiles += (uint64_t)((threads + 255) / 256);
-            cost += (uint64_t)((threads + 255) / 256) * rows * kVectorCost[h->model];
+            cost += (uint64_t)((threads + 255) / 256 * kVectorCost[h->model]) << log2_rows;
         }
         if (res) {
             img.nres = cnt;
@@ -531,19 +538,18 @@ int group_layout(mcl_lattice* const* hs, int count, const int64_t* n, const doub
         int part = 1;
         tiles = 0;
         for (int j = 0; j < cnt; ++j) {
-            const mcl_lattice* h = hs[order[j]];
-            const int64_t rows = rule.rows(replica(order[j]));
-            const uint64_t one = (uint64_t)rows * kVectorCost[h->model];
-            const uint64_t k = (uint64_t)((h->g.Q * (h->L / rows) + 255) / 256);
+            const Replica r = at(order[j]);
+            const int log2_rows = rule.log2_rows(r);
+            const uint64_t one = (uint64_t)kVectorCost[r.model] << log2_rows;
+            const uint64_t k = (uint64_t)(((r.vectors() >> log2_rows) + 255) / 256);
             for (; part < 8 && cost * part / 8 <= sum + k * one; ++part) share[part] = tiles + (cost * part / 8 - sum) / one;
             sum += k * one;
             tiles += k;
         }
         share[8] = tiles;
         for (int p = 0; p < 8; ++p) most = std::max(most, share[p + 1] - share[p]);
-        if (base)
-            for (int p = 0; p < 9; ++p)
-                ((uint32_t*)(base + img.off_s))[kShareWord + 9 * img.nlaunch + p] = (uint32_t)share[p];
+        for (int p = 0; p < 9; ++p)
+            ((uint32_t*)(base + img.off_s))[kShareWord + 9 * img.nlaunch + p] = (uint32_t)share[p];
         // one workgroup per tile of the longest share, or a persistent grid of
         // wg_per_cu per CU; a multiple of 8 either way (one share per XCD)
         uint64_t grid = 8 * most;
@@ -698,11 +704,10 @@ int group_run(mcl_lattice* const* hs, int count, const int64_t* n, const double*
     hipStream_t stream = hs[0]->stream;
     int devid = 0;
     MCL_HIP(hipGetDevice(&devid));
-    GroupImage img;
     std::vector<int> order((size_t)count);
-    int rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, nullptr, order.data());
-    if (rc) return rc;
-    if (img.nmax == 0 && img.res_nmax == 0) return MCL_OK;
+    const GroupRule rule(tun, count, Entries{hs, n});
+    GroupImage img = group_size(hs, count, n, rule);
+    if (img.ndesc == 0) return MCL_OK;
 
     DeviceSlots& ds = g_slots[devid];
     Slot& sl = ds.slot[ds.next];
@@ -723,7 +728,7 @@ int group_run(mcl_lattice* const* hs, int count, const int64_t* n, const double*
         MCL_HIP(hipMalloc(&sl.dev, cap));
         sl.cap = cap;
     }
-    rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, sl.host, order.data());
+    int rc = group_layout(hs, count, n, beta, D, tun, rule, compute_units(devid), img, (char*)sl.host, order.data());
     if (rc) return rc;
     MCL_HIP(hipMemcpyAsync(sl.dev, sl.host, img.bytes, hipMemcpyHostToDevice, stream));
 
@@ -1128,17 +1133,16 @@ int group_run_noalloc(mcl_lattice* const* hs, int count, const int64_t* n, const
     int rc = noalloc_setup(devid);
     if (rc) return rc;
     NoAllocDevice& st = g_noalloc[devid];
-    GroupImage img;
-    rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, nullptr, g_noalloc_order);
-    if (rc) return rc;
-    if (img.nmax == 0 && img.res_nmax == 0) return MCL_OK;
+    const GroupRule rule(tun, count, Entries{hs, n});
+    GroupImage img = group_size(hs, count, n, rule);
+    if (img.ndesc == 0) return MCL_OK;
     if (img.bytes > kNoAllocBytes) return MCL_ESCRATCH;
     // the host image is free once the copy of the last call (on any device) has run
     if (g_noalloc_last >= 0 && g_noalloc[g_noalloc_last].pending) {
         MCL_HIP(hipEventSynchronize(g_noalloc[g_noalloc_last].copied));
         g_noalloc[g_noalloc_last].pending = false;
     }
-    rc = group_layout(hs, count, n, beta, D, tun, compute_units(devid), img, g_noalloc_host, g_noalloc_order);
+    rc = group_layout(hs, count, n, beta, D, tun, rule, compute_units(devid), img, (char*)g_noalloc_host, g_noalloc_order);
     if (rc) return rc;
     // the device image is rewritten only after the launches of the previous
     // call on this device, whatever stream they were queued on
@@ -1530,7 +1534,7 @@ int mcl_group_rows(int count, const int* model, const int64_t* L, int32_t* rows)
     for (int i = 0; i < count; ++i) some += replica(i).L != 0;
     for (int i = 0; i < count; ++i) {
         const Replica r = replica(i);
-        rows[i] = some < 2 || r.L == 0 || rule.resident(r) ? 0 : (int32_t)rule.rows(r);
+        rows[i] = some < 2 || r.L == 0 || rule.resident(r) ? 0 : 1 << rule.log2_rows(r);
     }
     return MCL_OK;
 }
