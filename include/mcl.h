@@ -132,8 +132,13 @@ int lattice_init(mcl_lattice** out, int model, int64_t L, uint64_t seed, int ini
  * Small lattices take fewer launches than one per half-sweep: the smallest
  * (L <= 128, 1-bit cells 256) are held in one workgroup's LDS for the whole
  * call, others (up to L = 7168, 1-bit cells 12288) run two to four sweeps in
- * each pair of launches.  The environment variable MCL_SWEEP_GRAPH, read on
- * each call, replaces that by one launch per half-sweep (0), or by replays of
+ * each pair of launches; a single sweep (up to L = 3072, 1-bit cells 4096)
+ * takes a thread per word.  The pairs of launches are made for a lattice
+ * that has the GPU to itself: lattices from about L = 3500 on (Blume-Capel
+ * 2500, 1-bit 8000) that are swept on several streams at once run up to 1.6
+ * times faster with one launch per half-sweep.  The environment variable
+ * MCL_SWEEP_GRAPH, read on each call, replaces that by one launch per
+ * half-sweep (0), or by replays of
  * an executable HIP graph of 32 sweeps of such launches in calls of 32 sweeps
  * or more, at any size (1); a graph is captured on first use for each (beta, D)
  * (up to four per handle, destroyed by lattice_free) on a library stream of
@@ -208,14 +213,16 @@ int lattice_info(const mcl_lattice* h, int* model, int64_t* L, uint64_t* seed, i
 
 /* Batched path: advance `count` independent lattices (any mix of
  * models, sizes, beta and D) by n[i] sweeps each.  Replicas advance sweep by
- * sweep together.  Every lattice of L <= 2^17 with n[i] > 0 goes into one
- * launch per colour per sweep that covers all of them, all three models
- * alike (or, with the split_models tuning, one launch per model and
- * colour; many small lattices, or a call of nothing else, are first run in
- * LDS, a workgroup each, in one launch for all their sweeps): a persistent grid walks a list of tiles of 256 threads, each
- * tile one band of rows of one replica, so a replica's parameters are
- * wave-uniform.  Larger lattices fill the GPU alone and are swept one per
- * launch within the call.  All lattices must use the stream of hs[0], and
+ * sweep together.  Lattices of L <= 2^17 with n[i] > 0 go into one launch
+ * per colour per sweep that covers all of them, all three models alike (or,
+ * with the split_models tuning, one launch per model and colour): a grid
+ * walks a list of tiles of 256 threads, each tile one band of rows of one
+ * replica, so a replica's parameters are wave-uniform.  Many small
+ * lattices, or all of a call that has only small ones, are run in LDS
+ * instead, a workgroup each, in one launch for all their sweeps.  A call in
+ * which only one lattice of L <= 2^17 has work sweeps it as sweep() does.
+ * Larger lattices fill the GPU alone and are swept one per launch within
+ * the call.  All lattices must use the stream of hs[0], and
  * no two entries with n[i] > 0 may share device memory (the same handle
  * twice, or handles on overlapping buffers), which would race: MCL_EARG
  * otherwise, before anything is queued.  Every lattice ends bit-identical

@@ -12,9 +12,9 @@ LIB = os.path.join(HERE, "libmcl.so")
 SOURCES = ["api.hip", "sweep.hip", "measure.hip", "pass.hip", "full.hip", "batch.hip", "resident.hip",
            "io.hip"]  # calibrate.hip is a separate program
 
-# Packed-FP32 instructions are switched off for all device code; the
-# library has no floating point on the device, but the flag keeps the
-# compiler from ever emitting them.
+# Packed-FP32 instructions are switched off for all device code: the
+# measurement kernels sum in fp32 (matrix accumulators, and what is done with
+# them), and the compiler would make packed operations of that by itself.
 HIP_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -309,8 +309,8 @@ bool solo(mcl_lattice* const* hs, int count, const int64_t* n)
 // unit each).  us per sweep at 64 sweeps (at one), Ising / Blume-Capel, against
 // pairs of launches for several sweeps (and one launch per half-sweep): L = 128
 // 2.6 (4.6) / 3.7 (6.7) against 3.5 (7.8) / 5.0 (11.8); L = 192 5.6 / 7.3
-// against 3.6 / 4.9.  1-bit cells: L = 256 4.9 against 7.9, at one sweep 23.8
-// against 22.6.
+// against 3.6 / 4.9.  1-bit cells: L = 256 4.9 against 7.9; one sweep of them is
+// not worth the bucket table and takes a word per thread (7.0).
 bool resident_alone(const mcl_lattice* h, int64_t n)
 {
     if (h->model == MCL_ISING_LUT) return h->L <= 256 && n > 1;
@@ -321,9 +321,14 @@ bool resident_alone(const mcl_lattice* h, int64_t n)
 // in a compute unit's LDS (L = 384, 1-bit L = 512), or where every replica of
 // the call is of L <= 256 (1-bit 512).  They run before the batched launches, so
 // a few small replicas beside large ones are better off in those.  16 sweeps:
-// 64 of L = 256 184 against 311 us, 512 343 against 578, 256 of L = 384 402
-// against 651; 512 of L = 512, one to a compute unit, 1281 against 1450, but 128
-// of them 637 against 548.
+// 64 of L = 256 180 against 304 us, 512 289 against 540, 128 of L = 384 364
+// against 440, 256 373 against 638; 512 of L = 512, one to a compute unit, 1130
+// against 1449, but 128 of them 628 against 513.  A call of small ones only
+// goes this way however few they are: against the batched launches two to eight
+// of L = 256 take 41 against 82 us at four sweeps (19.2 against 17.5 at one),
+// 1-bit L = 512 86 against 140 (37.5 against 33.6).  Swept one after the other,
+// two of L = 256 would take 29 us and three 43, two 1-bit ones of L = 512 64 and
+// three 95; two of L = 64 12.6 against 19.2.
 constexpr int kResidentMany = 128;
 constexpr size_t kResidentGroupLds = 76 * 1024;
 
@@ -349,7 +354,11 @@ constexpr int64_t kResidentSweeps = 256;
 // last, partly filled one.  48 replicas of L = 512 .. 8192, 4 sweeps:
 // 2.02 ms, with 2^19 threads 2.29, 2^21 2.09, the tuning's bands 2.80.  1-bit
 // replicas take half the cap, as a row costs them twice as much and the last
-// tiles are waited for: 1.90 ms.
+// tiles are waited for: 1.90 ms.  Over 40 other calls (2 to 112 replicas of one
+// model or several, L = 256 .. 16384, 4 sweeps), the time with another number of
+// threads to that with 2^20: 2^18 1.04 on average (at most 1.48), 2^19 1.00
+// (1.08), 2^21 0.995 (1.02), 2^22 1.00 (1.08); with the full cap for 1-bit
+// replicas 1.00 (0.94 to 1.05).
 // The environment variable MCL_GROUP_ROWS (2 to 64, rounded down to a power of
 // two; read at every call) is the cap of every replica instead: calls that give
 // few threads then run the bands of those that give many, as a test does.

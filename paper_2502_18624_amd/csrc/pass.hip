@@ -28,9 +28,9 @@
 //
 // What it replaced counted xors of bit words, 2 to 3 VALU instructions per
 // 32 pairs of 64 distances, and was bound by VALU issue.  Measured, before and
-// after, the B/M/Q work included: 4-bit Ising L = 2^17 4.00 -> 1.96 ms (8.6 GB:
-// 4.4 TB/s, bound by memory reads: a kernel that only loads in this pattern
-// takes 1.42), 1-bit L = 2^16 0.85 -> 0.30 ms (matrix and VALU issue),
+// after, the B/M/Q work included: 4-bit Ising L = 2^17 4.00 -> 1.96 ms (8.6 GB of
+// lattice, 10.3 read with the strips' edge lines: 5.2 TB/s, bound by memory reads:
+// a kernel that only loads in this pattern takes 1.42), 1-bit L = 2^16 0.85 -> 0.30 ms (matrix and VALU issue),
 // Blume-Capel L = 2^15 0.87 -> 0.17 ms (0.54 GB: 3.1 TB/s; VALU issue beside
 // the reads).  Edge cells read from memory by each wave, not each workgroup,
 // made it 2.9 ms at L = 2^17.
@@ -59,6 +59,10 @@ constexpr int kTileRows = 32;               // rows of a tile: two blocks of 16
 // Blume-Capel L = 2^15 and 1-bit L = 2^16, one round with runs of 64, 2% slower).
 constexpr int kMaxTiles = 64;
 
+// 1-bit strips of 512 cells need 16 to 24 registers more than the 256 that two
+// waves per SIMD leave and keep them in scratch (68 to 100 bytes a lane): a
+// quench of L = 2^16 with three measurements takes 6.39 ms, without a spill, one
+// wave per SIMD, 6.54.
 // Strips: 256 four-bit cells (with 128, half a row of fragments per lane, the
 // measurement at L = 2^17 takes 2.50 against 2.36 ms), but 128 for
 // Blume-Capel, whose two bit planes of 256 need 148 registers more than there

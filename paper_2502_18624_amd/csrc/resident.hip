@@ -7,7 +7,7 @@
 // 256: 4.4 us for 2^15 updates, which are 0.012 us of the chip's VALU work).
 // Here a half-sweep costs a barrier and its work on one compute unit, bound by
 // VALU issue; the draws are keyed by (seed, sweep, site), so the lattice is
-// the same.  512 replicas of L = 256, 16 sweeps: 285 us, 78% of the VALU rate
+// the same.  512 replicas of L = 256, 16 sweeps: 280 us, 79% of the VALU rate
 // (the launches per half-sweep took 1190, or 580 with bands short enough to
 // fill their tiles).
 #include <algorithm>
@@ -33,7 +33,7 @@ constexpr size_t kMostLds = 150 * 1024;
 // L = 12288 42.6 against 50.4 (L = 16384 does not fit LDS in 256 tiles).
 constexpr int64_t kTrapezoidMaxL = 7168, kTrapezoidMaxLutL = 12288;
 // The largest whose single sweeps take a word per thread: L = 3072 12.1 against
-// 13.1 us (Blume-Capel 15.4, 16.9), 4096 19.2 against 13.6; 1-bit 4096 13.8
+// 13.1 us (Blume-Capel 15.4, 16.9), 4096 19.2 against 13.6; 1-bit 4096 11.5
 // against 27.6.
 constexpr int64_t kHalfWordsMaxL = 3072, kHalfWordsMaxLutL = 4096;
 
@@ -308,6 +308,14 @@ __global__ __launch_bounds__(kMaxThreads) void group_resident_kernel(const Group
 // L = 1024 6.6 against 23.3, 4096 8.5 against 23.9, 8192 20.2 against 25.1.  The
 // VALU work is about half of it from L = 3008 on; the rest is steps with less
 // than a round of work for the waves.
+//   That is a lattice alone on the chip.  Launches per half-sweep of lattices on
+// several streams fill each other's gaps better than these do: eight streams, L =
+// 2048 24.6 against 53.6 us for eight sweeps of a lattice (these against those),
+// 3008 48 against 56, but 3584 64 against 54, 4096 84 against 58, 7168 220
+// against 189 (Blume-Capel 2048 48 / 51, 3008 81 / 60, 4096 116 / 79; 1-bit 6144
+// 79 / 86, 8192 133 / 122, 12288 343 / 277).  Nothing tells a call what other
+// streams do, so the rule is the lone lattice's; MCL_SWEEP_GRAPH=0 has the
+// launches per half-sweep, and group_sweep takes many lattices together.
 // ---------------------------------------------------------------------------
 template <int MODEL, bool WORDS, bool CUTS>
 __global__ __launch_bounds__(kMaxThreads) void trapezoid_kernel(uint32_t* __restrict__ planes, uint32_t L, uint32_t tiles,
@@ -396,8 +404,8 @@ __global__ __launch_bounds__(kMaxThreads) void trapezoid_kernel(uint32_t* __rest
 // row steps of a band.  1-bit cells take the exact search, so that a single
 // sweep needs no bucket table.  One sweep in us, against the band kernels
 // (launching takes about 3.7 of each half): Ising L = 256 7.7 against 8.6, 2048
-// 7.9 against 9.6; Blume-Capel 8.0 against 12.6 and 9.9 against 13.6; 1-bit 9.4
-// against 22.2 and 10.9 against 27.4.
+// 7.9 against 9.6; Blume-Capel 8.0 against 12.6 and 9.9 against 13.6; 1-bit 7.0
+// against 22.2 and 7.5 against 27.4.
 // ---------------------------------------------------------------------------
 template <int MODEL>
 __global__ __launch_bounds__(256) void half_words_kernel(uint32_t* __restrict__ planes, uint32_t L, uint32_t c, uint32_t t,

@@ -16,7 +16,10 @@ namespace {
 // y & 1, odd x those of the other.  Bound by the generator's VALU work,
 // L^2 / 4 blocks: 1.24 ms for 1-bit cells at L = 2^16, where 40 lane
 // instructions a block take 1.09 (with a block per cell 5.44, with a compare
-// and a shift per cell 1.40); Blume-Capel 1.62 (1.94), Ising L = 2^17 5.8 (6.1).
+// and a shift per cell 1.40); Blume-Capel 1.62 (1.94), Ising L = 2^17 5.8 (6.1):
+// the least of repeated starts into one buffer.  The starts of a benchmark run,
+// into memory just allocated, take 1.9 to 2.1 ms (Blume-Capel L = 2^16), 6.1 to
+// 7.2 (Ising L = 2^17) and 5.5 (1-bit L = 2^17).
 // ---------------------------------------------------------------------------
 // Cells come in from the highest to the lowest, so that each takes one funnel
 // shift of its draw w: a 1-bit cell is w's top bit negated (+1 iff w < 2^31)
