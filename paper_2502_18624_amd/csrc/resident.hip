@@ -313,9 +313,14 @@ __global__ __launch_bounds__(kMaxThreads) void group_resident_kernel(const Group
 // 2048 24.6 against 53.6 us for eight sweeps of a lattice (these against those),
 // 3008 48 against 56, but 3584 64 against 54, 4096 84 against 58, 7168 220
 // against 189 (Blume-Capel 2048 48 / 51, 3008 81 / 60, 4096 116 / 79; 1-bit 6144
-// 79 / 86, 8192 133 / 122, 12288 343 / 277).  Nothing tells a call what other
-// streams do, so the rule is the lone lattice's; MCL_SWEEP_GRAPH=0 has the
-// launches per half-sweep, and group_sweep takes many lattices together.
+// 79 / 86, 8192 133 / 122, 12288 343 / 277).  Part of it: two workgroups of 16
+// waves share a compute unit only where the kernel takes no more than 80 scalar
+// registers (the wave's trap registers make it 96, of 800 a SIMD), which the
+// Blume-Capel and the vector forms exceed.  12 waves, or a limit on the
+// registers, give four streams 1.2 to 1.4 times as much at L = 2560 .. 5120, but
+// cost a lattice alone 1 to 5%.  Nothing tells a call what other streams do, so
+// the rule is the lone lattice's; MCL_SWEEP_GRAPH=0 has the launches per
+// half-sweep, and group_sweep takes many lattices together.
 // ---------------------------------------------------------------------------
 template <int MODEL, bool WORDS, bool CUTS>
 __global__ __launch_bounds__(kMaxThreads) void trapezoid_kernel(uint32_t* __restrict__ planes, uint32_t L, uint32_t tiles,
